@@ -501,7 +501,7 @@ rg_status make_verify_args(const uint16_t* logits, int64_t row_stride, int32_t v
   a.num_req = num_requests;
   a.rows = total_rows;
   a.nchunk = logit_chunks(vocab);
-  a.cshift = logit_chunk_shift(vocab);
+  chunk_divisor(vocab, a.cmul, a.cshift);
   a.row_indptr = row_indptr;
   a.tokens = draft_tokens;
   a.row_argmax = row_argmax;
@@ -510,8 +510,7 @@ rg_status make_verify_args(const uint16_t* logits, int64_t row_stride, int32_t v
   a.row_entropy = row_entropy;
   a.accept_entropy = accept_entropy;
   a.chunk_st = static_cast<float4*>(ws);
-  a.vec = (aligned(logits, 16) && row_stride % 8 == 0) ? 1 : 0;
-  a.grid_rows = (int32_t)round_up((int64_t)total_rows << a.cshift, 8);
+  a.grid_rows = (int32_t)round_up((int64_t)total_rows * a.nchunk, 8);
   return RG_OK;
 }
 
@@ -530,7 +529,7 @@ rg_status make_draft_args(const uint16_t* logits, int64_t row_stride, int32_t vo
   a.vocab = vocab;
   a.rows = total_rows;
   a.nchunk = logit_chunks(vocab);
-  a.cshift = logit_chunk_shift(vocab);
+  chunk_divisor(vocab, a.cmul, a.cshift);
   a.top1 = top1;
   a.top2 = top2;
   a.p1 = p1;
@@ -541,8 +540,7 @@ rg_status make_draft_args(const uint16_t* logits, int64_t row_stride, int32_t vo
   a.chunk_a = reinterpret_cast<float4*>(w);
   if (w != nullptr) w += align256((size_t)total_rows * a.nchunk * 16);
   a.chunk_b = reinterpret_cast<float2*>(w);
-  a.vec = (aligned(logits, 16) && row_stride % 8 == 0) ? 1 : 0;
-  a.grid_rows = (int32_t)round_up((int64_t)total_rows << a.cshift, 8);
+  a.grid_rows = (int32_t)round_up((int64_t)total_rows * a.nchunk, 8);
   return RG_OK;
 }
 

@@ -102,7 +102,8 @@ struct VerifyArgs {
   const uint16_t* logits;
   int64_t row_stride;
   int32_t vocab, num_req, rows, nchunk;
-  int32_t cshift;      // row work groups are slots of 2^cshift >= nchunk chunks
+  uint32_t cmul;       // item / nchunk = item * cmul >> cshift (chunk_divisor)
+  int32_t cshift;
   const int32_t* row_indptr;
   const int32_t* tokens;
   int32_t* row_argmax;
@@ -111,15 +112,15 @@ struct VerifyArgs {
   float* row_entropy;
   float* accept_entropy;
   float4* chunk_st;    // workspace [rows * nchunk] (max, bits(argmax), Z', S)
-  int32_t vec;         // 16-byte loads allowed
-  int32_t grid_rows;   // row work groups (rows << cshift rounded up to 8)
+  int32_t grid_rows;   // row work groups (rows * nchunk rounded up to 8)
 };
 
 struct DraftArgs {
   const uint16_t* logits;
   int64_t row_stride;
   int32_t vocab, rows, nchunk;
-  int32_t cshift;      // as in VerifyArgs
+  uint32_t cmul;         // as in VerifyArgs
+  int32_t cshift;
   int32_t* top1;
   int32_t* top2;
   float* p1;
@@ -128,17 +129,27 @@ struct DraftArgs {
   float* entropy;
   float4* chunk_a;       // workspace [rows * nchunk] (max, bits(i1), v2, bits(i2))
   float2* chunk_b;       // [rows * nchunk] (Z', S)
-  int32_t vec;
   int32_t grid_rows;
 };
 
 inline int32_t logit_chunks(int32_t vocab) { return (vocab + kLogitChunk - 1) / kLogitChunk; }
-// log2 of the chunk slots per row: the smallest power of two >= the row's
-// chunks, so a row work group finds its row and chunk by shift and mask.
+// log2 of the smallest power of two >= a row's chunks: with it the accepted
+// sizes are bounded (rows << shift fits 30 bits).
 inline int32_t logit_chunk_shift(int32_t vocab) {
   int32_t s = 0;
   while ((1 << s) < logit_chunks(vocab)) ++s;
   return s;
+}
+// Division of an item index (below 2^31) by the chunks per row: with
+// l = logit_chunk_shift, mul = ceil(2^(31 + l) / nchunk) fits 32 bits, and
+// item * mul >> (31 + l) is exact, since mul * nchunk exceeds 2^(31 + l) by
+// less than nchunk <= 2^l, so the product is off by less than 2^(31 + l).  A
+// row work group thus finds its row and chunk with one scalar multiply and
+// no work groups are launched for slots past a row's last chunk.
+inline void chunk_divisor(int32_t vocab, uint32_t& mul, int32_t& shift) {
+  const uint64_t n = (uint64_t)logit_chunks(vocab);
+  shift = 31 + logit_chunk_shift(vocab);
+  mul = (uint32_t)(((uint64_t(1) << shift) + n - 1) / n);
 }
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 

@@ -308,3 +308,29 @@ def test_random_rounds(i):
     check_verify(vlog, rp.cpu().numpy(), tok, fv)
     if nd_total:
         check_draft(dlog, fd)
+
+
+@pytest.mark.parametrize("vocab", [7, 8, 9, 15, 8191, 8192, 8193, 8199, 3 * 8192 + 5, 65537])
+def test_rows_at_any_two_byte_place(vocab):
+    """Rows that start at every 2-byte place of a 16-byte word (odd row
+    strides, offset bases), with row ends in every part of a load's eight
+    entries: larger values all around the rows show an entry that is read
+    past a row's end, or counted twice."""
+    g = torch.Generator(device=DEV).manual_seed(vocab)
+    for offset, pad in ((0, 1), (1, 2), (3, 4), (5, 0)):
+        rows = 11
+        flat = torch.full((offset + rows * (vocab + pad) + 16,), 3e4, dtype=torch.bfloat16, device=DEV)
+        logits = flat[offset:offset + rows * (vocab + pad)].view(rows, vocab + pad)[:, :vocab]
+        x = torch.randn(rows, vocab, generator=g, device=DEV) * 2
+        x[1, -1], x[2, 0] = 9.0, 9.0                # the maximum at either end
+        x[3, -1], x[3, 0] = 9.0, 9.0                # and at both
+        x[4, max(0, vocab - 9)], x[5, vocab - 2] = 9.0, 9.0
+        logits.copy_(x.to(torch.bfloat16))
+        rp = torch.tensor([0, 4, 4, rows], dtype=torch.int32, device=DEV)
+        tok = torch.argmax(logits.float(), dim=1).to(torch.int32)
+        tok[7] = (tok[7] + 1) % vocab
+        dense = logits.contiguous()                 # the oracle's copy
+        res = binding.verify_accept(logits, rp, tok)
+        torch.cuda.synchronize()
+        check_verify(dense, rp.cpu().numpy(), tok, res)
+        check_draft(dense, run_draft(logits))
