@@ -184,7 +184,10 @@ rg_status rg_draft_verify_attention(const rg_attn_layout* layout, const uint16_t
 rg_status rg_draft_verify_attention_check(void* ws, size_t ws_bytes, void* stream);
 
 /* Planning summary of an attention call (host only, no GPU work): used by
- * tests and tools to inspect how the batch is split. */
+ * tests and tools to inspect how the batch is split.  It describes the finest
+ * split a call uses, which sizes the workspace; a two-launch call may give a
+ * work group a longer run of keys than chunk_keys, where one round of work
+ * groups is faster than two, and then writes fewer partials. */
 typedef struct rg_attn_plan_info {
   int32_t num_launches;     /* launches of the main kernel                   */
   int32_t chunk_keys;       /* keys per KV chunk                             */

@@ -116,7 +116,8 @@ rg_status validate_branches(const rg_attn_layout* L, const rg_branch_layout* B) 
 template <typename Plan>
 struct FullPlanT {
   std::vector<Plan> launches;
-  int chunk = 0;
+  int chunk = 0;      // the finest split: it sizes the workspace and orders one-launch calls
+  int run = 0;        // keys per work item of the launches, >= chunk
   int cols_per_group = 256;
   int64_t items = 0, split_requests = 0, max_partial_cols = 0, total_partial_cols = 0;
   int64_t max_comb = 0;
@@ -191,8 +192,67 @@ int choose_chunk(const std::vector<int64_t>& pair_keys, int hkv, int num_cus) {
   return (int)(hi * kKeyTile);
 }
 
-// Branch words of request r (see AttnReqBr); all zero when B is NULL or
-// the request lists no branch.
+// One (request, column group) of the batch; it stands for Hkv pairs.
+struct PairLoad {
+  int64_t keys;
+  double weight;  // time per buffer at the copy rate: tile_weight of the request
+};
+
+// Time of one 128-key buffer of an item with this many 32-column tiles, in
+// units of a buffer at the copy rate: wide items are bound by their MFMA and
+// softmax work, not by the copies.
+double tile_weight(int64_t tiles) { return std::max(1.0, (double)tiles / 4.0); }
+
+// Keys per work item that the two-launch kernels really take: `chunk` (the
+// workspace's split, in at most two rounds of `num_cus` items) or longer.
+// When the whole requests give at most one round of items, one round of the
+// shortest items that fit it is usually faster than two rounds of about half
+// the length: it pays an item's start-up and wind-down (about 6 us) once and
+// writes half the partials.  Not when a few items would then be much longer
+// than the rest, as two rounds even the loads out: one round is taken when
+// its longest item is at most 1.35 mean loads of a compute unit plus 512 keys
+// (about one start-up).  And where no request is longer than such an item by
+// more than 192 keys at the copy rate, requests stay whole: the merge kernel
+// (4 to 5 us) costs more than the keys.
+// Measured on 70 drawn batches with both splits forced (GPU time of the
+// call): this rule is within 0.1 % of the better one on average, always two
+// rounds 17 % off, always one round 2 %.  E.g. one round against two: 27.0
+// and 39.3 us (26 requests of up to 3.6k keys, 2 KV heads), 24.5 and 34.7 us
+// (one of 17.5k), 59.8 and 74.3 us (15 of up to 5.9k), but 198 and 163 us (55
+// of up to 11k keys with branches, D = 64).  More than one round of whole
+// requests: unchanged.
+int choose_run(const std::vector<PairLoad>& pairs, int hkv, int num_cus, int chunk) {
+  const int64_t cus = std::max(1, num_cus);
+  int64_t total = 0, longest = 0;
+  for (const PairLoad& p : pairs) {
+    total += p.keys;
+    longest = std::max(longest, p.keys);
+  }
+  if ((int64_t)pairs.size() * hkv > cus || longest <= chunk) return chunk;
+  auto fits = [&](int64_t bufs) {
+    int64_t n = 0;
+    for (const PairLoad& p : pairs) n += (p.keys + bufs * kKeyTile - 1) / (bufs * kKeyTile);
+    return n * hkv <= cus;
+  };
+  // Buffers per item: `lo` or fewer cannot fit or are below the chunk (all
+  // keys over the items of a round), the longest request's do fit.
+  int64_t lo = std::max<int64_t>(chunk / kKeyTile - 1, (total * hkv + cus * kKeyTile - 1) / (cus * kKeyTile) - 1);
+  int64_t hi = std::max<int64_t>(lo + 1, (longest + kKeyTile - 1) / kKeyTile);
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) / 2;
+    if (fits(mid)) hi = mid;
+    else lo = mid;
+  }
+  const int64_t run = hi * kKeyTile;
+  double load = 0.0, item = 0.0, extra = 0.0;
+  for (const PairLoad& p : pairs) {
+    load += (double)p.keys * p.weight;
+    item = std::max(item, (double)std::min(run, p.keys) * p.weight);
+    extra = std::max(extra, (double)(p.keys - run) * p.weight);
+  }
+  if (item > 1.35 * load * hkv / cus + 512.0) return chunk;
+  return (int)std::min<int64_t>(kMaxChunkKeys, extra <= 192.0 ? round_up(longest, kKeyTile) : run);
+}
 
 // Launches with a split request run as the main kernel plus the combine
 // kernel, or, with RG_ATTN_PERSIST=1, as one work-queue launch (main items,
@@ -211,19 +271,25 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
   const int hkv = L->num_kv_heads;
   fp.cols_per_group = 256;  // 8 waves x 32 columns per work group
   std::vector<int64_t> pair_keys;  // one entry per (request, column group): Hkv pairs each
+  std::vector<PairLoad> pairs;     // the same, with their weights
   for (int r = 0; r < R; ++r) {
     const int64_t n = L->q_indptr[r + 1] - L->q_indptr[r];
     if (n == 0) continue;
     const int64_t ncg = (n * g + fp.cols_per_group - 1) / fp.cols_per_group;
-    for (int64_t cg = 0; cg < ncg; ++cg) pair_keys.push_back((int64_t)L->ctx_len[r] + n);
+    const int64_t T = (int64_t)L->ctx_len[r] + n;
+    const double weight = tile_weight(((n * g + 31) / 32 + ncg - 1) / ncg);
+    for (int64_t cg = 0; cg < ncg; ++cg) {
+      pair_keys.push_back(T);
+      pairs.push_back({T, weight});
+    }
   }
   fp.chunk = choose_chunk(pair_keys, hkv, num_cus);
+  fp.run = persist || env_int("RG_ATTN_CHUNK", 0) > 0 ? fp.chunk : choose_run(pairs, hkv, num_cus, fp.chunk);
   // Costliest work items first: work groups are dispatched in item order, so
   // the long items start early and the short ones fill in at the end.  An
   // item's time is estimated in units of one 128-key buffer at the copy rate:
-  // about two units of start-up plus its buffers, each costing
-  // max(1, tiles / 4) units for its 32-column tiles -- wide items are bound
-  // by their MFMA and softmax work, not by the copies.  A request's items all
+  // about two units of start-up plus its buffers, each costing tile_weight
+  // units.  A request's items all
   // get the estimate of its widest column group's full-chunk item.  The
   // divisor was picked by measurement: against ordering by keys alone, over 4
   // `long` and 10 `mid` draws, the divisors 4 and 5.6 and a linear
@@ -236,8 +302,8 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
     const int64_t all_tiles = (n * g + 31) / 32;
     const int64_t groups = std::max<int64_t>(1, (all_tiles + 7) / 8);
     const int64_t tiles = (all_tiles + groups - 1) / groups;  // the widest column group's (tiles dealt evenly)
-    const int64_t bufs = (std::min<int64_t>(T, fp.chunk) + kKeyTile - 1) / kKeyTile;
-    cost[r] = n == 0 ? 0.0 : 2.0 + (double)bufs * std::max(1.0, (double)tiles / 4.0);
+    const int64_t bufs = (std::min<int64_t>(T, fp.run) + kKeyTile - 1) / kKeyTile;
+    cost[r] = n == 0 ? 0.0 : 2.0 + (double)bufs * tile_weight(tiles);
   }
   std::vector<int> order(R);
   for (int r = 0; r < R; ++r) order[r] = r;
@@ -251,9 +317,10 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
     Plan p;
     std::memset(&p, 0, sizeof(p));
     p.num_req = cnt;
-    p.chunk = fp.chunk;
+    p.chunk = fp.run;
     p.cols_per_group = fp.cols_per_group;
-    int64_t items = 0, part = 0, comb = 0;
+    int64_t items = 0, part = 0, comb = 0;    // of the launch
+    int64_t plan_items = 0, plan_part = 0;    // at the workspace's split
     for (int k = 0; k < cnt; ++k) {
       const int r = order[r0 + k];
       const int64_t n = L->q_indptr[r + 1] - L->q_indptr[r];
@@ -269,17 +336,22 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
       if (n == 0) continue;
       const int64_t M = n * g;
       const int64_t T = (int64_t)L->ctx_len[r] + n;
-      const int64_t nch = (T + fp.chunk - 1) / fp.chunk;
+      const int64_t nch = (T + fp.run - 1) / fp.run;
       const int64_t ncg = (M + fp.cols_per_group - 1) / fp.cols_per_group;
       items += hkv * ncg * nch;
+      const int64_t plan_nch = (T + fp.chunk - 1) / fp.chunk;
+      plan_items += hkv * ncg * plan_nch;
+      if (plan_nch > 1) {
+        plan_part += hkv * plan_nch * round_up(M, 32);
+        fp.split_requests += 1;
+      }
       if (nch > 1) {
         p.max_chunks = std::max<int32_t>(p.max_chunks, (int32_t)nch);
         // partials are stored per 32-column tile, so columns round up to 32
         part += hkv * nch * round_up(M, 32);
         comb += hkv * ((M + 31) / 32) * (L->head_dim * 4 / comb_rows);  // slices of a tile's 4 D rows
-        fp.split_requests += 1;
       }
-      if (items > INT32_MAX / 2 || part > INT32_MAX / 2) return RG_ERR_UNSUPPORTED;
+      if (plan_items > INT32_MAX / 2 || plan_part > INT32_MAX / 2) return RG_ERR_UNSUPPORTED;
     }
     p.req[cnt].item_start = (int32_t)items;
     p.req[cnt].part_start = (int32_t)part;
@@ -292,9 +364,9 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
       p.persist_grid = (int32_t)round_up(std::min<int64_t>(items + comb, std::max(8, num_cus)), 8);
       fp.persistent_launches += 1;
     }
-    fp.items += items;
-    fp.max_partial_cols = std::max(fp.max_partial_cols, part);
-    fp.total_partial_cols += part;
+    fp.items += plan_items;
+    fp.max_partial_cols = std::max(fp.max_partial_cols, plan_part);
+    fp.total_partial_cols += plan_part;
     fp.max_comb = std::max(fp.max_comb, comb);
     fp.launches.push_back(p);
   }

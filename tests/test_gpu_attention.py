@@ -322,3 +322,30 @@ def test_full_size_configs_sampled(name, samples):
                                       lay.ctx_len[r:r + 1], pi, pidx)
         q0, q1 = int(lay.q_indptr[r]), int(lay.q_indptr[r + 1])
         check(out[q0:q1], lse[q0:q1], ref)
+
+
+@pytest.mark.parametrize("case", [
+    dict(ctx=[1500] * 7, nv=[5] * 7, nd=[6] * 7),                              # one round, several chunks per request
+    dict(ctx=[300, 2400, 700], nv=[8] * 3, nd=[8] * 3, hq=32, hkv=8),          # one round, some requests whole
+    dict(ctx=[513, 520, 250, 300], nv=[4] * 4, nd=[4] * 4, hq=32, hkv=8),      # whole: little longer than a run
+    dict(ctx=[4000] + [150] * 15, nv=[3] * 16, nd=[5] * 16, hq=32, hkv=8),     # skewed: one request far longer
+    dict(ctx=[260] * 32, nv=[2] * 32, nd=[2] * 32, hq=32, hkv=8),              # 256 whole items: exactly one round
+    dict(ctx=[260] * 33, nv=[2] * 33, nd=[2] * 33, hq=32, hkv=8),              # 264: more than one
+    dict(ctx=[900, 40, 1300], nv=[20, 1, 9], nd=[60, 2, 70], hq=16, hkv=2),    # several column groups
+    dict(ctx=[1700, 90, 0, 800], nv=[7, 0, 0, 2], nd=[9, 3, 0, 5], D=64, hq=8, hkv=4),
+])
+def test_runs_of_one_round(case):
+    """Batches on either side of the rule that gives a work item more keys
+    than the workspace's split: the results, and that the call stays within
+    a workspace of the queried size."""
+    kw = {k: case[k] for k in ("hq", "hkv", "D") if k in case}
+    lay = _custom(len(case["ctx"]), case["ctx"], case["nv"], case["nd"], **kw)
+    inp = W.make_attention_inputs(lay, DEV, poison=float("nan"))
+    layout = binding.make_layout(inp["q"], inp["k_cache"], lay.q_indptr, lay.n_verify, lay.ctx_len, lay.page_indptr,
+                                 torch.as_tensor(lay.page_indices, device=DEV))
+    need = binding.attention_workspace_bytes(layout)
+    buf = torch.zeros(need + 4096, dtype=torch.uint8, device=DEV)
+    buf[need:] = 0xA5
+    out, lse = run(lay, inp, layout=layout, workspace=buf[:need] if need else None)
+    check(out, lse, reference(lay, inp))
+    assert (buf[need:] == 0xA5).all()
