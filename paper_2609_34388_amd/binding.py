@@ -130,6 +130,8 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _dev(t: torch.Tensor, name: str, dtype: torch.dtype) -> torch.Tensor:
+    if type(t) is torch.Tensor and t.dtype is dtype and t.is_cuda and t.is_contiguous():
+        return t
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA (HIP) tensor")
     if t.dtype != dtype:
@@ -148,12 +150,29 @@ def _host_i32(x, name: str) -> np.ndarray:
     return a
 
 
+# The current stream's raw handle without building a torch.cuda.Stream around
+# it (2.7 us of a call's 8 to 27): where this torch has the function.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
+
+
+def _outputs(given: Optional[Dict[str, torch.Tensor]], device, *wanted) -> Dict[str, torch.Tensor]:
+    """The caller's outputs, and a new tensor for each (name, size, dtype)
+    of `wanted` that is not among them."""
+    o = dict(given or {})
+    for name, size, dtype in wanted:
+        if name not in o:
+            o[name] = torch.empty(size, dtype=dtype, device=device)
+    return o
 
 
 def _check(status: int, where: str):
@@ -233,9 +252,10 @@ def draft_verify_attention(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torc
         lse = torch.empty(q.shape[0], q.shape[1], dtype=torch.float32, device=q.device)
     if lse is not None:
         _dev(lse, "lse", torch.float32)
-    need = attention_workspace_bytes(lay)
-    if workspace is None and need:
-        workspace = new_workspace(need, q.device)
+    if workspace is None:  # the call itself checks the size of one that is given
+        need = attention_workspace_bytes(lay)
+        if need:
+            workspace = new_workspace(need, q.device)
     ws_ptr = _ptr(workspace) if workspace is not None else None
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     st = _lib().rg_draft_verify_attention(ctypes.byref(lay.c), q.data_ptr(), k_cache.data_ptr(),
@@ -302,9 +322,10 @@ def multibranch_attention(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch
         lse = torch.empty(q.shape[0], q.shape[1], dtype=torch.float32, device=q.device)
     if lse is not None:
         _dev(lse, "lse", torch.float32)
-    need = multibranch_workspace_bytes(layout, branches)
-    if workspace is None and need:
-        workspace = new_workspace(need, q.device)
+    if workspace is None:  # the call itself checks the size of one that is given
+        need = multibranch_workspace_bytes(layout, branches)
+        if need:
+            workspace = new_workspace(need, q.device)
     ws_ptr = _ptr(workspace) if workspace is not None else None
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     st = _lib().rg_multibranch_attention(ctypes.byref(layout.c), ctypes.byref(branches.c), q.data_ptr(),
@@ -445,13 +466,10 @@ def verify_accept(logits: torch.Tensor, row_indptr: torch.Tensor, draft_tokens: 
     if rows:
         _dev(draft_tokens, "draft_tokens", torch.int32)
     dev = logits.device
-    o = dict(out or {})
-    o.setdefault("row_argmax", torch.empty(rows, dtype=torch.int32, device=dev))
-    o.setdefault("accept_len", torch.empty(R, dtype=torch.int32, device=dev))
-    o.setdefault("next_token", torch.empty(R, dtype=torch.int32, device=dev))
+    i, f = torch.int32, torch.float32
+    o = _outputs(out, dev, ("row_argmax", rows, i), ("accept_len", R, i), ("next_token", R, i))
     if want_entropy:
-        o.setdefault("row_entropy", torch.empty(rows, dtype=torch.float32, device=dev))
-        o.setdefault("accept_entropy", torch.empty(R, dtype=torch.float32, device=dev))
+        o = _outputs(o, dev, ("row_entropy", rows, f), ("accept_entropy", R, f))
     if workspace is None:
         workspace = new_workspace(verify_accept_workspace_bytes(R, rows, vocab), dev)
     st = _lib().rg_verify_accept(
@@ -472,13 +490,12 @@ def draft_confidence(logits: torch.Tensor, *, workspace: Optional[torch.Tensor] 
         raise TypeError("logits must be a CUDA bf16 [rows, vocab] tensor with unit column stride")
     rows, vocab = logits.shape
     dev = logits.device
-    o = dict(out or {})
-    for k, dt in (("top1", torch.int32), ("top2", torch.int32), ("p1", torch.float32), ("p2", torch.float32)):
-        o.setdefault(k, torch.empty(rows, dtype=dt, device=dev))
+    i, f = torch.int32, torch.float32
+    o = _outputs(out, dev, ("top1", rows, i), ("top2", rows, i), ("p1", rows, f), ("p2", rows, f))
     if want_margin:
-        o.setdefault("margin", torch.empty(rows, dtype=torch.float32, device=dev))
+        o = _outputs(o, dev, ("margin", rows, f))
     if want_entropy:
-        o.setdefault("entropy", torch.empty(rows, dtype=torch.float32, device=dev))
+        o = _outputs(o, dev, ("entropy", rows, f))
     if workspace is None:
         workspace = new_workspace(draft_confidence_workspace_bytes(rows, vocab), dev)
     st = _lib().rg_draft_confidence(
@@ -518,16 +535,11 @@ def verify_and_confidence(verify_logits: torch.Tensor, row_indptr: torch.Tensor,
     if vrows:
         _dev(draft_tokens, "draft_tokens", torch.int32)
     dev = verify_logits.device
-    ov = dict(out_verify or {})
-    ov.setdefault("row_argmax", torch.empty(vrows, dtype=torch.int32, device=dev))
-    ov.setdefault("accept_len", torch.empty(R, dtype=torch.int32, device=dev))
-    ov.setdefault("next_token", torch.empty(R, dtype=torch.int32, device=dev))
-    ov.setdefault("row_entropy", torch.empty(vrows, dtype=torch.float32, device=dev))
-    ov.setdefault("accept_entropy", torch.empty(R, dtype=torch.float32, device=dev))
-    od = dict(out_draft or {})
-    for k, dt in (("top1", torch.int32), ("top2", torch.int32), ("p1", torch.float32), ("p2", torch.float32),
-                  ("margin", torch.float32), ("entropy", torch.float32)):
-        od.setdefault(k, torch.empty(drows, dtype=dt, device=dev))
+    i, f = torch.int32, torch.float32
+    ov = _outputs(out_verify, dev, ("row_argmax", vrows, i), ("accept_len", R, i), ("next_token", R, i),
+                  ("row_entropy", vrows, f), ("accept_entropy", R, f))
+    od = _outputs(out_draft, dev, ("top1", drows, i), ("top2", drows, i), ("p1", drows, f), ("p2", drows, f),
+                  ("margin", drows, f), ("entropy", drows, f))
     args = (verify_logits.data_ptr() if vrows else None, verify_logits.stride(0) if vrows else vocab,
             draft_logits.data_ptr() if drows else None, draft_logits.stride(0) if drows else vocab, vocab, R, vrows,
             row_indptr.data_ptr(), draft_tokens.data_ptr() if vrows else None,
