@@ -39,6 +39,14 @@ constexpr int kU = kLogitChunk / (8 * kLogitThreads);  // 16-byte loads per thre
 constexpr int kE = 8 * kU;                             // entries per thread
 constexpr int kNoIndex = 0x7fffffff;
 constexpr int kBatchRows = 1024;                       // verify rows scanned per pass
+// Threads of a finalize work group: at 16 lanes per row (vocabularies of 8 to
+// 16 chunks) one pass takes 32 rows, so a request's usual block is merged in
+// one chain of load, merge and exchange, each of which costs about 1 us.
+// With the merges by DPP, against 256 threads (two passes at 17 to 32 rows)
+// and ds_bpermute: 6.1 -> 4.6 us at 16 requests of 4 to 32 verify rows, 5.8 ->
+// 3.9 us at 40 of 3 to 17.  Three passes' loads at once in 256 threads, with
+// the code three times as long, took 6.4 us.
+constexpr int kFinalizeThreads = 512;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));  // 16 bytes at any 2-byte place
@@ -374,12 +382,14 @@ struct State {
   float s;
 };
 
+// DRAFT: with the runner-up (verify rows have none).
+template <bool DRAFT>
 __device__ __forceinline__ State merge(const State& a, const State& b) {
   const bool a_wins = better(a.m, a.i1, b.m, b.i1);
   const State& w = a_wins ? a : b;
   const State& l = a_wins ? b : a;
   State o = w;
-  if (better(l.m, l.i1, w.v2, w.i2)) { o.v2 = l.m; o.i2 = l.i1; }
+  if (DRAFT && better(l.m, l.i1, w.v2, w.i2)) { o.v2 = l.m; o.i2 = l.i1; }
   if (l.m != kNegInf) {
     const float d = l.m - w.m;
     const float f = __builtin_amdgcn_exp2f(d * kLog2e);
@@ -390,9 +400,21 @@ __device__ __forceinline__ State merge(const State& a, const State& b) {
   return o;
 }
 
-__device__ __forceinline__ State shfl_state(const State& x, int off) {
-  return State{__shfl_xor(x.m, off), __shfl_xor(x.i1, off), __shfl_xor(x.v2, off),
-               __shfl_xor(x.i2, off), __shfl_xor(x.zp, off), __shfl_xor(x.s, off)};
+// The state of a lane OFF away, in the other half of its 2 OFF lanes.  Within
+// 16 lanes by DPP, one instruction per word and no trip through LDS: xor 1,
+// xor 2, and for 4 and 8 the half-row and row mirror, whose source lane holds
+// what lane xor OFF does, as the OFF lanes merged before are all alike.
+template <int OFF>
+__device__ __forceinline__ int lane_off(int v) {
+  if constexpr (OFF == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);
+  else if constexpr (OFF == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);
+  else if constexpr (OFF == 4) return __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);
+  else if constexpr (OFF == 8) return __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true);
+  else return __shfl_xor(v, OFF);
+}
+template <int OFF>
+__device__ __forceinline__ float lane_off(float v) {
+  return __int_as_float(lane_off<OFF>(__float_as_int(v)));
 }
 
 // Lanes per row when a row's chunk states are merged by a lane group: the
@@ -403,20 +425,35 @@ __device__ __forceinline__ int group_lanes(int nchunk) {
   return l;
 }
 
+// One butterfly step over groups of `lanes` lanes.
+template <bool DRAFT, int OFF>
+__device__ __forceinline__ void merge_step(int lanes, int j, State& acc) {
+  if (OFF >= lanes) return;  // uniform
+  State o{lane_off<OFF>(acc.m), lane_off<OFF>(acc.i1), kNegInf, kNoIndex, lane_off<OFF>(acc.zp), lane_off<OFF>(acc.s)};
+  if (DRAFT) {
+    o.v2 = lane_off<OFF>(acc.v2);
+    o.i2 = lane_off<OFF>(acc.i2);
+  }
+  acc = (j & OFF) ? merge<DRAFT>(o, acc) : merge<DRAFT>(acc, o);  // same operand order in both partners
+}
+
 // A group of `lanes` consecutive lanes merges `count` states: lane j of the
 // group takes states j, j + lanes, ... in order, then a fixed butterfly
 // combines the group.  Every lane of the group ends with the result.  All
 // states of all groups are fetched at once, so a pass costs one round trip.
-template <typename Fetch>
+template <bool DRAFT, typename Fetch>
 __device__ __forceinline__ State group_merge(int lanes, int count, bool active, Fetch fetch) {
   const int j = (threadIdx.x & 63) & (lanes - 1);
   State acc{kNegInf, kNoIndex, kNegInf, kNoIndex, 0.f, 0.f};
+  if (active && j < count) acc = fetch(j);
   if (active)
-    for (int k = j; k < count; k += lanes) acc = merge(acc, fetch(k));
-  for (int off = 1; off < lanes; off <<= 1) {
-    const State o = shfl_state(acc, off);
-    acc = (j & off) ? merge(o, acc) : merge(acc, o);  // same operand order in both partners
-  }
+    for (int k = j + lanes; k < count; k += lanes) acc = merge<DRAFT>(acc, fetch(k));
+  merge_step<DRAFT, 1>(lanes, j, acc);
+  merge_step<DRAFT, 2>(lanes, j, acc);
+  merge_step<DRAFT, 4>(lanes, j, acc);
+  merge_step<DRAFT, 8>(lanes, j, acc);
+  merge_step<DRAFT, 16>(lanes, j, acc);
+  merge_step<DRAFT, 32>(lanes, j, acc);
   return acc;
 }
 
@@ -455,19 +492,19 @@ __device__ __forceinline__ void verify_finalize(const VerifyArgs& a, int r, Fina
   const int k0 = a.row_indptr[r], k1 = a.row_indptr[r + 1];
   const int nrows = k1 - k0;
   const int lanes = group_lanes(a.nchunk);
-  const int per_pass = kLogitThreads / lanes;  // rows merged per pass
+  const int per_pass = kFinalizeThreads / lanes;  // rows merged per pass
   int acc_len = nrows;  // kept by wave 0
   int next = -1;
   bool found = false;
   float hsum = 0.f;
   for (int b0 = 0; b0 < nrows; b0 += kBatchRows) {
     const int nb = min(kBatchRows, nrows - b0);
-    for (int j = tid; j < nb; j += kLogitThreads) s_tok[j] = a.tokens[k0 + b0 + j];
+    for (int j = tid; j < nb; j += kFinalizeThreads) s_tok[j] = a.tokens[k0 + b0 + j];
     for (int i0 = 0; i0 < nb; i0 += per_pass) {
       const int i = i0 + tid / lanes;
       const bool active = i < nb;
       const float4* cs = a.chunk_st + (size_t)(k0 + b0 + (active ? i : 0)) * a.nchunk;
-      const State st = group_merge(lanes, a.nchunk, active, [&](int k) {
+      const State st = group_merge<false>(lanes, a.nchunk, active, [&](int k) {
         const float4 q = cs[k];
         return State{q.x, __float_as_int(q.y), kNegInf, kNoIndex, q.z, q.w};
       });
@@ -513,7 +550,7 @@ __device__ __forceinline__ void verify_finalize(const VerifyArgs& a, int r, Fina
   }
 }
 
-__global__ __launch_bounds__(kLogitThreads) void verify_finalize_kernel(VerifyArgs a) {
+__global__ __launch_bounds__(kFinalizeThreads) void verify_finalize_kernel(VerifyArgs a) {
   __shared__ FinalizeLds lds;
   verify_finalize(a, blockIdx.x, lds);
 }
@@ -539,13 +576,13 @@ __global__ __launch_bounds__(kLogitThreads) void draft_rows_kernel(DraftArgs a) 
   if (item < a.rows * a.nchunk) draft_rows(a, item, red);
 }
 
-// Draft rows blk * (256 / lanes) ...: one lane group per row.
+// Draft rows blk * (kFinalizeThreads / lanes) ...: one lane group per row.
 __device__ __forceinline__ void draft_finalize(const DraftArgs& a, int blk) {
   const int lanes = group_lanes(a.nchunk);
-  const int row = blk * (kLogitThreads / lanes) + (int)threadIdx.x / lanes;
+  const int row = blk * (kFinalizeThreads / lanes) + (int)threadIdx.x / lanes;
   const bool active = row < a.rows;
   const size_t base = (size_t)(active ? row : 0) * a.nchunk;
-  const State st = group_merge(lanes, a.nchunk, active, [&](int k) {
+  const State st = group_merge<true>(lanes, a.nchunk, active, [&](int k) {
     const float4 q = a.chunk_a[base + k];
     const float2 w = a.chunk_b[base + k];
     return State{q.x, __float_as_int(q.y), q.z, __float_as_int(q.w), w.x, w.y};
@@ -562,7 +599,7 @@ __device__ __forceinline__ void draft_finalize(const DraftArgs& a, int blk) {
   }
 }
 
-__global__ __launch_bounds__(kLogitThreads) void draft_finalize_kernel(DraftArgs a) { draft_finalize(a, blockIdx.x); }
+__global__ __launch_bounds__(kFinalizeThreads) void draft_finalize_kernel(DraftArgs a) { draft_finalize(a, blockIdx.x); }
 
 // Both passes of one round in two launches: the row items of the verify rows
 // and of the draft rows share one grid, and so do the two finalize steps.
@@ -574,7 +611,7 @@ __global__ __launch_bounds__(kLogitThreads) void round_rows_kernel(VerifyArgs v,
   else if (item - nv < d.rows * d.nchunk) draft_rows(d, item - nv, red);
 }
 
-__global__ __launch_bounds__(kLogitThreads) void round_finalize_kernel(VerifyArgs v, DraftArgs d) {
+__global__ __launch_bounds__(kFinalizeThreads) void round_finalize_kernel(VerifyArgs v, DraftArgs d) {
   __shared__ FinalizeLds lds;
   const int b = blockIdx.x;
   if (b < v.num_req) verify_finalize(v, b, lds);
@@ -584,7 +621,7 @@ __global__ __launch_bounds__(kLogitThreads) void round_finalize_kernel(VerifyArg
 int draft_finalize_groups(const DraftArgs& a) {
   int lanes = 1;
   while (lanes < a.nchunk && lanes < 64) lanes <<= 1;
-  const int rows_per_group = kLogitThreads / lanes;
+  const int rows_per_group = kFinalizeThreads / lanes;
   return (a.rows + rows_per_group - 1) / rows_per_group;
 }
 
@@ -626,7 +663,7 @@ hipError_t launch_verify(const VerifyArgs& a, hipStream_t stream) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(verify_finalize_kernel, dim3(a.num_req), dim3(kLogitThreads), 0, stream, a);
+  hipLaunchKernelGGL(verify_finalize_kernel, dim3(a.num_req), dim3(kFinalizeThreads), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -635,7 +672,7 @@ hipError_t launch_draft(const DraftArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL(draft_rows_kernel, dim3(a.grid_rows), dim3(kLogitThreads), 0, stream, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(draft_finalize_kernel, dim3(draft_finalize_groups(a)), dim3(kLogitThreads), 0, stream, a);
+  hipLaunchKernelGGL(draft_finalize_kernel, dim3(draft_finalize_groups(a)), dim3(kFinalizeThreads), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -648,7 +685,7 @@ hipError_t launch_round(const VerifyArgs& v, const DraftArgs& d, hipStream_t str
     if (e != hipSuccess) return e;
   }
   const int blocks = v.num_req + (d.rows > 0 ? draft_finalize_groups(d) : 0);
-  hipLaunchKernelGGL(round_finalize_kernel, dim3(blocks), dim3(kLogitThreads), 0, stream, v, d);
+  hipLaunchKernelGGL(round_finalize_kernel, dim3(blocks), dim3(kFinalizeThreads), 0, stream, v, d);
   return hipGetLastError();
 }
 
