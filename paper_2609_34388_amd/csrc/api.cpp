@@ -195,6 +195,7 @@ int choose_chunk(const std::vector<int64_t>& pair_keys, int hkv, int num_cus) {
 // One (request, column group) of the batch; it stands for Hkv pairs.
 struct PairLoad {
   int64_t keys;
+  int64_t tiles;  // 32-column tiles
   double weight;  // time per buffer at the copy rate: tile_weight of the request
 };
 
@@ -254,6 +255,38 @@ int choose_run(const std::vector<PairLoad>& pairs, int hkv, int num_cus, int chu
   return (int)std::min<int64_t>(kMaxChunkKeys, extra <= 192.0 ? round_up(longest, kKeyTile) : run);
 }
 
+// Whether a call's items, of at most `run` keys, run in narrow work groups (4
+// compute and 2 copy waves on 128 columns, 64 keys per buffer, two to a CU)
+// or in full ones.  A narrow group starts sooner (half the waves, half the
+// first buffer, fewer key groups to merge) and a second one on the CU computes
+// while the first starts or ends; but a CU that holds only one has half the
+// waves, and barriers and copies are twice as many per key.  So narrow groups
+// take short items; at head size 64, where a buffer is half the bytes and the
+// softmax is the longer part, also every call of more than one round; and at
+// 128, where items have one or two tiles and the copies are the longer part,
+// also medium ones.  Measured on 160 drawn batches with both kinds (GPU time
+// of the call, full over narrow):
+//   items of at most 512 keys, more than one round: 1.13 to 1.37 (70 requests
+//     of 140 to 500 keys, 42.6 and 31.2 us);
+//   at most one round: to 512 keys at D = 64 1.02 to 1.14, to 256 at D = 128
+//     1.02 to 1.15, where 384 keys of 3 or 4 tiles give 0.97 to 1.02;
+//   D = 64, more than one round: 1.015 to 1.27; at most one round of longer
+//     items: 0.89 to 0.98;
+//   D = 128, one or two tiles, up to 2432 keys: 1.02 to 1.34; longer: 0.96 to
+//     1.02;
+//   D = 128, three or four tiles, longer items: 0.79 to 1.02.
+bool narrow_items(const std::vector<PairLoad>& pairs, int hkv, int num_cus, int head_dim, int run) {
+  int64_t items = 0, tiles = 0;
+  for (const PairLoad& p : pairs) {
+    items += (p.keys + run - 1) / run * hkv;
+    tiles = std::max(tiles, p.tiles);
+  }
+  const bool one_round = items <= std::max(1, num_cus);
+  if (tiles > kNarrowCols / 32) return false;
+  if (head_dim == 64) return !one_round || run <= 512;
+  return run <= (tiles <= 2 ? 2432 : one_round ? 256 : 512);
+}
+
 // Launches with a split request run as the main kernel plus the combine
 // kernel, or, with RG_ATTN_PERSIST=1, as one work-queue launch (main items,
 // then the combine items; `num_cus` work groups at most).  The two launches
@@ -277,14 +310,20 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
     if (n == 0) continue;
     const int64_t ncg = (n * g + fp.cols_per_group - 1) / fp.cols_per_group;
     const int64_t T = (int64_t)L->ctx_len[r] + n;
-    const double weight = tile_weight(((n * g + 31) / 32 + ncg - 1) / ncg);
+    const int64_t tiles = ((n * g + 31) / 32 + ncg - 1) / ncg;
+    // more than one column group: never narrow
+    const int64_t pair_tiles = ncg > 1 ? 8 : tiles;
     for (int64_t cg = 0; cg < ncg; ++cg) {
       pair_keys.push_back(T);
-      pairs.push_back({T, weight});
+      pairs.push_back({T, pair_tiles, tile_weight(tiles)});
     }
   }
   fp.chunk = choose_chunk(pair_keys, hkv, num_cus);
   fp.run = persist || env_int("RG_ATTN_CHUNK", 0) > 0 ? fp.chunk : choose_run(pairs, hkv, num_cus, fp.chunk);
+  const bool narrow = narrow_items(pairs, hkv, num_cus, L->head_dim, fp.run);
+  // One round of narrow items is two to a CU: requests just over the split stay whole.
+  if (narrow && fp.run == fp.chunk && !persist && env_int("RG_ATTN_CHUNK", 0) == 0)
+    fp.run = choose_run(pairs, hkv, 2 * num_cus, fp.chunk);
   // Costliest work items first: work groups are dispatched in item order, so
   // the long items start early and the short ones fill in at the end.  An
   // item's time is estimated in units of one 128-key buffer at the copy rate:
@@ -319,6 +358,7 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
     p.num_req = cnt;
     p.chunk = fp.run;
     p.cols_per_group = fp.cols_per_group;
+    p.narrow = narrow ? 1 : 0;
     int64_t items = 0, part = 0, comb = 0;    // of the launch
     int64_t plan_items = 0, plan_part = 0;    // at the workspace's split
     for (int k = 0; k < cnt; ++k) {

@@ -133,15 +133,24 @@ __device__ __forceinline__ float2 load8_coherent(const float* p) {
   return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
 }
 
-constexpr int kWaves = 8;      // compute waves per work group (two per SIMD)
-constexpr int kProducers = 4;  // copy waves per work group (one per SIMD)
-constexpr int kThreads = 64 * (kWaves + kProducers);
-constexpr int kSuper = 128;  // keys staged per LDS buffer (four 32-key sub-tiles)
+constexpr int kWaves = 8;        // compute waves of a full work group (two per SIMD), 256 columns
+constexpr int kNarrowWaves = 4;  // ... of a narrow one, 128 columns, two to a CU
+constexpr int threads_of(int waves) { return 64 * (waves + waves / 2); }  // with one copy wave per two
+constexpr int kThreads = threads_of(kWaves);
+// Keys staged per LDS buffer of a work group of `waves` compute waves.
+constexpr int super_keys(int waves) { return 16 * waves; }
 constexpr int kKBufs = 2;    // K buffers: one computed, one being filled
 constexpr int kVBufs = 2;    // V buffers: one computed, one being filled
 static_assert(kKBufs == 2 && kVBufs == 2, "two copy-wave pairs, one per buffer parity and LDS slot");
-static_assert(kSuper % kKeyTile == 0, "a super-tile is a whole number of key tiles");
 
+// A full work group (NW = 8) takes up to 256 columns and has a CU to itself.
+// A narrow one (NW = 4, launches without a request of more than 128 columns)
+// halves everything per group: waves, columns, keys per buffer and LDS, so
+// that two share a CU with the same copies in flight together, and one
+// computes while the other starts or ends.  The comments below describe the
+// full group.  Which launches take which is the host's rule (narrow_items,
+// with both measured).
+//
 // Work group = 8 compute waves over (column tiles) x (key groups).  A
 // request's columns are split into groups of up to 256 (8 tiles of 32); a
 // wave handling key group kgi of kg processes the chunk's 32-key sub-tiles j
@@ -163,19 +172,21 @@ static_assert(kSuper % kKeyTile == 0, "a super-tile is a whole number of key til
 // then passes the same barriers (the copy waves join the key-group merge),
 // and a split item's partials are stored device-coherently and counted so
 // that the combine items of the same launch can merge them.
-template <int D, typename Plan, bool PERSIST>
+template <int D, typename Plan, bool PERSIST, int NW>
 __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, const int item, uint16_t* lds) {
   constexpr bool BR = __is_same(Plan, AttnPlanBr);  // rows after the verify rows form branches
   constexpr int NCH = D / 8;                   // 16-byte chunks per K row
   constexpr int KSTEPS = D / 16;               // MFMA k-steps of q.k
   constexpr int DT = D / 32;                   // 32-wide head-dim tiles of the output
-  constexpr int SUPER = kSuper * D;            // bf16 elements of one K (or V) buffer
+  constexpr int KEYS = super_keys(NW);         // keys of one buffer
+  constexpr int PAGES = KEYS / kPageSize;      // pages of one buffer
+  constexpr int SUPER = KEYS * D;              // bf16 elements of one K (or V) buffer
   constexpr int BLOCKS = SUPER * 2 / 1024;     // 1 KiB copy blocks per K (or V) buffer
   constexpr int KPB = 1024 / (2 * D);          // keys per K block
   constexpr int VBPP = D / 32;                 // V blocks per page
-  constexpr int COLS = 32 * kWaves;            // columns per column group
+  constexpr int COLS = 32 * NW;                // columns per column group
   // key-group merge: one slot per wave that hands its state over (every such wave has index >= 1)
-  static_assert((kKBufs + kVBufs) * SUPER * 2 >= (kWaves - 1) * (64 * 16 * DT + 128) * 4, "merge area");
+  static_assert((kKBufs + kVBufs) * SUPER * 2 >= (NW - 1) * (64 * 16 * DT + 128) * 4, "merge area");
 
   // kbuf[b] = K of 128 keys ([key][D], 16-byte chunks swizzled per row),
   // vbuf[b] = V of 8 pages ([page][D][16 keys], halves swizzled per row).
@@ -221,7 +232,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
   // tiles 0-3 get waves 0-3 and the rest share waves 4-7 by key groups, so
   // no SIMD carries two whole tiles while another idles.
   const int nct = min(tpg, (M + 31) / 32 - cg * tpg);
-  const bool producer = wave >= kWaves;  // wave-uniform: copy wave
+  const bool producer = wave >= NW;  // wave-uniform: copy wave
   // Pages of this chunk: entries pg0 .. pg0 + npg - 1 of the request's list.
   const int pg0 = kbeg / kPageSize;
   const int npg = (kend + kPageSize - 1) / kPageSize - pg0;
@@ -241,42 +252,43 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
   // buffer (i = 0 .. NB - 1): a K block is KPB keys, a V block 32 head dims of
   // one page, 1 KiB each; lane L's 16 bytes of a block go to byte 16 L of the
   // block's place in the slot.  A wave reads its buffer's 8 page numbers
-  // (one batch of scalar loads), loads its blocks into registers and writes
+  // (one scalar load), loads its blocks into registers and writes
   // them to LDS before the buffer's barrier.  Page slots past the chunk's
   // last page repeat that page, so buffer rows past the chunk end hold other
   // tokens or unused slots of the last page (memory of the pool either way);
   // their scores are masked and their values zeroed before use.
-  constexpr int WPG = kProducers / 2;  // copy waves per parity
+  constexpr int WPG = NW / 4;         // copy waves per parity
   constexpr int NB = BLOCKS / WPG;     // K (and V) blocks per copy wave and buffer
   static_assert(BLOCKS % WPG == 0 && NB % 2 == 0, "blocks split evenly over a pair");
-  const int pw = wave - kWaves;
+  const int pw = wave - NW;
   const int par = pw / WPG;  // wave-uniform: buffer parity (and LDS slot) of this copy wave
   const int q = pw % WPG;
   // A buffer's 8 page numbers: one 32-byte scalar load when all 8 are the
   // chunk's (else one load per slot, repeating the last page), so the copies
   // wait for one scalar round trip, not eight.
-  typedef int32_t i32x8 __attribute__((ext_vector_type(8), aligned(4)));
-  typedef const i32x8 __attribute__((address_space(4))) * cpage8_ptr;
-  static_assert(kSuper / kPageSize == 8, "eight pages per buffer");
-  auto read_pages = [&](int s, int (&pg)[kSuper / kPageSize]) {
-    const int base = s * (kSuper / kPageSize);
-    if (base + 8 <= npg) {
-      const i32x8 v = *(cpage8_ptr)(chunk_pages + base);
+  typedef int32_t pages_vec __attribute__((ext_vector_type(PAGES), aligned(4)));
+  typedef const pages_vec __attribute__((address_space(4))) * cpages_ptr;
+  static_assert(PAGES == 4 || PAGES == 8, "one scalar load of page numbers");
+  auto read_pages = [&](int s, int (&pg)[PAGES]) {
+    const int base = s * PAGES;
+    if (base + PAGES <= npg) {
+      const pages_vec v = *(cpages_ptr)(chunk_pages + base);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) pg[j] = v[j];
+      for (int j = 0; j < PAGES; ++j) pg[j] = v[j];
     } else {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) pg[j] = chunk_pages[min(base + j, npg - 1)];
+      for (int j = 0; j < PAGES; ++j) pg[j] = chunk_pages[min(base + j, npg - 1)];
     }
   };
-  // A lane's byte offset inside its page repeats with period 2 in i: blocks
-  // i and i + 2 lie 2 WPG = 4 blocks apart, 4 KPB keys (a multiple of 16,
-  // so the same page slot and the same swap23 row bits) or 4 V blocks (a
-  // multiple of VBPP, so the same head dims).
-  static_assert((2 * WPG * KPB) % kPageSize == 0 && (2 * WPG) % VBPP == 0, "offsets repeat every two blocks");
-  uint32_t koff[2], voff[2];
+  // A lane's byte offset inside its page repeats with period PER in i: blocks
+  // i and i + PER lie PER WPG = 4 blocks apart (2 at D = 64 in a narrow work
+  // group), a multiple of 16 keys (so the same page slot and the same swap23
+  // row bits) and of VBPP V blocks (so the same head dims).
+  constexpr int PER = (WPG * KPB * 2) % kPageSize == 0 && (WPG * 2) % VBPP == 0 ? 2 : 4;
+  static_assert((PER * WPG * KPB) % kPageSize == 0 && (PER * WPG) % VBPP == 0, "offsets repeat every PER blocks");
+  uint32_t koff[PER], voff[PER];
 #pragma unroll
-  for (int e = 0; e < 2; ++e) {
+  for (int e = 0; e < PER; ++e) {
     const int b = q + WPG * e;
     const int kk = b * KPB + lane / NCH;
     koff[e] = (uint32_t)((((kk % kPageSize) * D) + (((lane % NCH) ^ (swap23(kk & 31) & (NCH - 1))) * 8)) * 2);
@@ -284,17 +296,17 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
     voff[e] = (uint32_t)((d * kPageSize + ((lane & 1) ^ vswz(d)) * 8) * 2);
   }
   // This wave's blocks of one buffer: NB K blocks, then NB V blocks.
-  auto load_set = [&](const int (&pg)[kSuper / kPageSize], u32x4 (&r)[2 * NB]) {
+  auto load_set = [&](const int (&pg)[PAGES], u32x4 (&r)[2 * NB]) {
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int b = q + WPG * i;
       r[i] = __builtin_nontemporal_load(
-          (const u32x4*)(kbase_g + (size_t)pg[(b * KPB) / kPageSize] * page_bytes + koff[i & 1]));
+          (const u32x4*)(kbase_g + (size_t)pg[(b * KPB) / kPageSize] * page_bytes + koff[i % PER]));
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int b = q + WPG * i;
-      r[NB + i] = __builtin_nontemporal_load((const u32x4*)(vbase_g + (size_t)pg[b / VBPP] * page_bytes + voff[i & 1]));
+      r[NB + i] = __builtin_nontemporal_load((const u32x4*)(vbase_g + (size_t)pg[b / VBPP] * page_bytes + voff[i % PER]));
     }
   };
   auto store_set = [&](const u32x4 (&r)[2 * NB]) {
@@ -307,13 +319,13 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
     }
   };
 
-  const int nsup = (kend - kbeg + kSuper - 1) / kSuper;
+  const int nsup = (kend - kbeg + KEYS - 1) / KEYS;
   // Zero the values of keys past the chunk end in the last buffer (every
   // wave takes part, so both loops below pass the same barriers), by 16-byte
   // units (page slot pp, head dim d, half h = keys 16 pp + 8 h ..).
   auto tail_fixup = [&](int s, int nvalid) {
     uint16_t* vz = vbuf(s);
-    for (int u = tid; u < (kSuper / kPageSize) * D * 2; u += kThreads) {
+    for (int u = tid; u < PAGES * D * 2; u += threads_of(NW)) {
       const int pp = u / (2 * D), d = (u >> 1) % D, h = u & 1;
       const int kfirst = kPageSize * pp + 8 * h;
       if (kfirst + 8 <= nvalid) continue;
@@ -335,7 +347,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
     // A pair reads the page numbers of its next buffer right after issuing
     // the loads of the current one, so they are in registers when needed.
     u32x4 r[2 * NB];
-    int pg[kSuper / kPageSize];
+    int pg[PAGES];
     if (par < nsup) {
       read_pages(par, pg);
       load_set(pg, r);
@@ -345,15 +357,15 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
       const bool mine = (s & 1) == par;
       if (mine) store_set(r);
       lds_barrier();  // everyone's copies of buffer s are in; buffers of s - 1 are no longer read
-      const int nvalid = kend - (kbeg + s * kSuper);
-      if (nvalid < kSuper) tail_fixup(s, nvalid);
+      const int nvalid = kend - (kbeg + s * KEYS);
+      if (nvalid < KEYS) tail_fixup(s, nvalid);
       if (mine && s + 2 < nsup) {
         load_set(pg, r);  // buffer s + 2, whose page numbers were fetched a round earlier
         if (s + 4 < nsup) read_pages(s + 4, pg);
       }
     }
     if constexpr (PERSIST) {
-      if (nct < 8) {  // the key-group merge's two barriers
+      if (nct < NW) {  // the key-group merge's two barriers
         lds_barrier();
         lds_barrier();
       }
@@ -364,7 +376,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
   if (nct <= 4) {
     const int nct2 = nct <= 1 ? 1 : nct <= 2 ? 2 : 4;
     ct = wave % nct2;
-    kg = kWaves / nct2;
+    kg = NW / nct2;
     kgi = wave / nct2;
     kstride = nct2;
   } else if (wave < 4 || nct == 8) {
@@ -526,15 +538,15 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
   };
   for (int s = 0; s < nsup; ++s) {
     lds_barrier();
-    const int k0 = kbeg + s * kSuper;
+    const int k0 = kbeg + s * KEYS;
     const int nvalid = kend - k0;
-    if (nvalid < kSuper) tail_fixup(s, nvalid);
+    if (nvalid < KEYS) tail_fixup(s, nvalid);
     if (tile_on) {
       const uint16_t* kt = kbuf(s);
       const uint16_t* vt = vbuf(s);
-      // this wave's sub-tiles of the buffer: global sub-tile j = 4 s + q with j % kg == kgi
-      for (int q = 0; q < kSuper / 32; ++q)
-        if (((4 * s + q) & (kg - 1)) == kgi && 32 * q < nvalid) softmax_pv(qk(kt, q), k0 + 32 * q, vt, q);
+      // this wave's sub-tiles of the buffer: global sub-tile j = KEYS / 32 s + q with j % kg == kgi
+      for (int q = 0; q < KEYS / 32; ++q)
+        if (((KEYS / 32 * s + q) & (kg - 1)) == kgi && 32 * q < nvalid) softmax_pv(qk(kt, q), k0 + 32 * q, vt, q);
     }
   }
 
@@ -542,12 +554,12 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
   // Merge the key groups' partial states (lane-wise: same columns, same dims).
   // A wave's slot holds its accumulator as 16-byte rows, lane-interleaved.
   float l_tot = l_run + __shfl_xor(l_run, 32);
-  if (nct < 8) {  // some tile is split over key groups (uniform: every compute wave passes the barriers)
+  if (NW == 8 ? nct < 8 : nct <= 2) {  // some tile is split over key groups (uniform: every compute wave passes the barriers)
     lds_barrier();  // every wave is done with the buffers before they are reused
     float* area = reinterpret_cast<float*>(lds);
-    constexpr int PER = 64 * 16 * DT + 128;  // floats per wave slot
+    constexpr int SLOT = 64 * 16 * DT + 128;  // floats per wave slot
     if (tile_on && kgi > 0) {
-      float* slot = area + (wave - 1) * PER;
+      float* slot = area + (wave - 1) * SLOT;
       for (int dt = 0; dt < DT; ++dt)
         for (int ib = 0; ib < 4; ++ib)
           *(float4*)(slot + ((dt * 4 + ib) * 64 + lane) * 4) =
@@ -558,7 +570,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
     lds_barrier();
     if (!tile_on || kgi > 0) return;
     for (int k = 1; k < kg; ++k) {
-      const float* slot = area + (wave + k * kstride - 1) * PER;
+      const float* slot = area + (wave + k * kstride - 1) * SLOT;
       const float mk = slot[64 * 16 * DT + lane];
       if (mk == kNegInf) continue;
       const float lk = slot[64 * 16 * DT + 64 + lane];
@@ -789,12 +801,12 @@ __device__ __forceinline__ void combine_item(const AttnArgs& a, const Plan& p, c
 // dispatch order.  One request: its heads' chunk ranges go to one XCD each
 // (shared q and page list in that XCD's L2).  Several: dispatch order, so the
 // costliest requests, which come first, spread over all XCDs.
-template <int D, typename Plan>
-__global__ __launch_bounds__(kThreads) void attn_fwd_kernel(AttnArgs a, Plan p) {
-  __shared__ __attribute__((aligned(16))) uint16_t lds[(kKBufs + kVBufs) * kSuper * D];
+template <int D, int NW, typename Plan>
+__global__ __launch_bounds__(threads_of(NW), 3) void attn_fwd_kernel(AttnArgs a, Plan p) {
+  __shared__ __attribute__((aligned(16))) uint16_t lds[(kKBufs + kVBufs) * super_keys(NW) * D];
   const int item = p.num_req == 1 ? xcd_item(p.grid_items) : (int)blockIdx.x;
   if (item >= p.total_items) return;
-  attn_item<D, Plan, false>(a, p, item, lds);
+  attn_item<D, Plan, false, NW>(a, p, item, lds);
 }
 
 template <int D, int PARTS, typename Plan>
@@ -823,8 +835,8 @@ __global__ __launch_bounds__(kCombRows * PARTS) void attn_combine_kernel(AttnArg
 // it: the flag does not carry over into the next call.
 template <int D, typename Plan>
 __global__ __launch_bounds__(kThreads) void attn_persist_kernel(AttnArgs a, Plan p) {
-  constexpr int WORDS = (kKBufs + kVBufs) * kSuper * D / 2;  // 32-bit words of LDS (all of it)
-  __shared__ __attribute__((aligned(16))) uint16_t lds[(kKBufs + kVBufs) * kSuper * D];
+  constexpr int WORDS = (kKBufs + kVBufs) * super_keys(kWaves) * D / 2;  // 32-bit words of LDS (all of it)
+  __shared__ __attribute__((aligned(16))) uint16_t lds[(kKBufs + kVBufs) * super_keys(kWaves) * D];
   // The next item's index passes through the last word of the second V
   // buffer: no key-group merge area or combine exchange reaches it, and an
   // item writes that buffer only after its first barrier (buffer 1 goes in
@@ -841,7 +853,7 @@ __global__ __launch_bounds__(kThreads) void attn_persist_kernel(AttnArgs a, Plan
     int nxt = total;
     if (threadIdx.x == 0) nxt = __hip_atomic_fetch_add(a.sync, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (item < p.total_items)
-      attn_item<D, Plan, true>(a, p, item, lds);
+      attn_item<D, Plan, true, kWaves>(a, p, item, lds);
     else
       combine_item<D, kCombPartsPersist, kCombRowsPersist, true>(a, p, item - p.total_items,
                                                                 reinterpret_cast<float*>(lds));
@@ -869,7 +881,12 @@ hipError_t launch_impl(const AttnArgs& args, const Plan& plan, hipStream_t strea
                        plan);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((attn_fwd_kernel<D, Plan>), dim3(plan.grid_items), dim3(kThreads), 0, stream, args, plan);
+  if (plan.narrow)
+    hipLaunchKernelGGL((attn_fwd_kernel<D, kNarrowWaves, Plan>), dim3(plan.grid_items),
+                       dim3(threads_of(kNarrowWaves)), 0, stream, args, plan);
+  else
+    hipLaunchKernelGGL((attn_fwd_kernel<D, kWaves, Plan>), dim3(plan.grid_items), dim3(kThreads), 0, stream, args,
+                       plan);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (plan.total_comb > 0) {

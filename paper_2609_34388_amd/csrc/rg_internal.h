@@ -12,6 +12,7 @@ namespace rg {
 constexpr int kPageSize = 16;
 constexpr int kMaxReqPerLaunch = 128;  // equals RG_ATTN_MAX_REQS_PER_LAUNCH
 constexpr int kKeyTile = 128;          // keys per LDS buffer; chunks are multiples of it
+constexpr int kNarrowCols = 128;       // query columns of a narrow attention work group
 constexpr int kMaxChunkKeys = 1 << 16;  // keys per work item at most
 constexpr int kSyncHeader = 4;          // queue head, exit count, give-up flag, report word
 // Combine items of one launch the one-launch kernel can count (two counters
@@ -63,6 +64,7 @@ struct AttnPlanT {
   int32_t persist_grid;    // 0: main kernel + combine kernel; else the work groups of the
                            // one-launch work-queue kernel (main items, then combine items)
   Req req[MaxReq + 1];     // entry num_req holds the end sentinels
+  int32_t narrow;          // 1: narrow work groups (no request has more than 128 columns)
 };
 using AttnPlan = AttnPlanT<AttnReq, kMaxReqPerLaunch>;
 using AttnPlanBr = AttnPlanT<AttnReqBr, kMaxReqPerLaunchBr>;

@@ -110,6 +110,31 @@ def test_edge_cases(case):
     check(out, lse, reference(lay, inp))
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("g", [1, 4])
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("chunk", [0, 128])
+def test_narrow_and_full_work_groups(monkeypatch, D, g, full, chunk):
+    """Short requests of 1 to 128 columns around the edges of the 32-column
+    tiles and of the 32-, 64- and 128-key buffers, in narrow work groups and,
+    beside a request of more than 128 columns, in full ones; whole and split."""
+    if chunk:
+        monkeypatch.setenv("RG_ATTN_CHUNK", str(chunk))
+    cols = [1, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128]
+    keys = [1, 63, 64, 65, 127, 128, 129, 191, 193, 257, 449]
+    rows = [max(1, c // g) for c in cols]
+    total = [max(n, k) for n, k in zip(rows, keys)]
+    if full:
+        rows.append(128 // g + 1)
+        total.append(300)
+    nv = [n // 3 for n in rows]
+    lay = _custom(len(rows), [t - n for t, n in zip(total, rows)], nv, [n - v for n, v in zip(rows, nv)],
+                  hq=2 * g, hkv=2, D=D, seed=D + g)
+    inp = W.make_attention_inputs(lay, DEV, poison=float("nan"))
+    out, lse = run(lay, inp)
+    check(out, lse, reference(lay, inp))
+
+
 def _random_case(i):
     """Seeded random layout i of the sweep: shapes, GQA group, head size,
     empty and long requests, and a forced or automatic chunk size."""
