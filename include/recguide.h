@@ -305,7 +305,8 @@ rg_status rg_verify_and_confidence_noalloc(const uint16_t* verify_logits, int64_
  * ------------------------------------------------------------------------ */
 
 /* Largest number of requests planned into one multi-branch attention launch
- * (larger batches are split into several launches by the library). */
+ * (larger batches are split into several launches by the library, which sends
+ * two together where their requests fit a packed form). */
 #define RG_BRANCH_MAX_REQS_PER_LAUNCH 64
 
 /*

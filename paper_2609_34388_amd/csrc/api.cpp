@@ -468,6 +468,33 @@ rg_status plan_branched(const rg_attn_layout* layout, const rg_branch_layout* br
   return plan_attention<AttnPlanBr, kMaxReqPerLaunchBr>(layout, branches, fp, num_cus);
 }
 
+// Two launches' plans of branched requests as one, where no request of either
+// is split and all fit the packed form.  One launch lets the second plan's
+// items fill the compute units that the first one's last round leaves idle.
+// Measured: 128 requests of 512-4096 tokens with three branches each 260 -> 245
+// us; 14 drawn batches of 65 to 159 requests 1.066x on average, 0.994 to 1.164.
+// Dealing the requests alternately to the two launches instead: 251 us, but
+// 0.76 to 1.08x on those batches, since each launch starts a round of its own.
+bool join_plans(const AttnPlanBr& a, const AttnPlanBr& b, AttnPlanBrPacked& p) {
+  if (a.total_comb > 0 || b.total_comb > 0 || a.total_items == 0 || b.total_items == 0) return false;
+  std::memset(&p, 0, sizeof(p));
+  p.num_req = a.num_req + b.num_req;
+  p.chunk = a.chunk;
+  p.total_items = a.total_items + b.total_items;
+  p.grid_items = (int32_t)round_up(p.total_items, 8);
+  p.cols_per_group = a.cols_per_group;
+  p.narrow = a.narrow;
+  for (int k = 0; k < a.num_req; ++k)
+    if (!p.req[k].pack(a.req[k])) return false;
+  for (int k = 0; k < b.num_req; ++k) {
+    AttnReqBr r = b.req[k];
+    r.item_start += a.total_items;
+    if (!p.req[a.num_req + k].pack(r)) return false;
+  }
+  p.req[p.num_req].item_start = p.total_items;
+  return true;
+}
+
 template <typename Plan>
 rg_status run_attention(const rg_attn_layout* layout, const FullPlanT<Plan>& fp, const uint16_t* q,
                         const uint16_t* k_cache, const uint16_t* v_cache, uint16_t* out, float* lse,
@@ -495,7 +522,16 @@ rg_status run_attention(const rg_attn_layout* layout, const FullPlanT<Plan>& fp,
   a.scale_log2 = a.sm_scale * 1.4426950408889634f;
   a.rescale_gap = 8.0f / a.scale_log2;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  for (const Plan& p : fp.launches) {
+  for (size_t l = 0; l < fp.launches.size(); ++l) {
+    const Plan& p = fp.launches[l];
+    if constexpr (__is_same(Plan, AttnPlanBr)) {
+      AttnPlanBrPacked both;
+      if (l + 1 < fp.launches.size() && join_plans(p, fp.launches[l + 1], both)) {
+        if (launch_attention(a, both, layout->head_dim, s) != hipSuccess) return RG_ERR_HIP;
+        ++l;
+        continue;
+      }
+    }
     if (p.total_items == 0) continue;
     if (launch_attention(a, p, layout->head_dim, s) != hipSuccess) return RG_ERR_HIP;
   }

@@ -73,7 +73,9 @@ __device__ __forceinline__ int find_request(const Plan& p, int item, bool combin
   int r = 0;
   for (int base = 1; base < p.num_req; base += 64) {
     const int k = base + lane;
-    const bool le = k < p.num_req && (combine ? p.req[k].comb_start : p.req[k].item_start) <= item;
+    bool le = k < p.num_req;
+    if constexpr (__is_same(Plan, AttnPlanBrPacked)) le = le && p.req[k].item_start <= item;
+    else le = le && (combine ? p.req[k].comb_start : p.req[k].item_start) <= item;
     r += __popcll(__ballot(le));
   }
   return __builtin_amdgcn_readfirstlane(r);
@@ -172,9 +174,13 @@ static_assert(kKBufs == 2 && kVBufs == 2, "two copy-wave pairs, one per buffer p
 // then passes the same barriers (the copy waves join the key-group merge),
 // and a split item's partials are stored device-coherently and counted so
 // that the combine items of the same launch can merge them.
+__device__ __forceinline__ AttnReq request_of(const AttnPlan& p, int r) { return p.req[r]; }
+__device__ __forceinline__ AttnReqBr request_of(const AttnPlanBr& p, int r) { return p.req[r]; }
+__device__ __forceinline__ AttnReqBr request_of(const AttnPlanBrPacked& p, int r) { return p.req[r].unpack(); }
+
 template <int D, typename Plan, bool PERSIST, int NW>
 __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, const int item, uint16_t* lds) {
-  constexpr bool BR = __is_same(Plan, AttnPlanBr);  // rows after the verify rows form branches
+  constexpr bool BR = !__is_same(Plan, AttnPlan);  // rows after the verify rows form branches
   constexpr int NCH = D / 8;                   // 16-byte chunks per K row
   constexpr int KSTEPS = D / 16;               // MFMA k-steps of q.k
   constexpr int DT = D / 32;                   // 32-wide head-dim tiles of the output
@@ -196,7 +202,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
   auto vbuf = [&](int s) { return lds + (kKBufs + s % kVBufs) * SUPER; };
 
   const int r = find_request(p, item, false);
-  const auto rq = p.req[r];
+  const auto rq = request_of(p, r);
   // both counts are 16-bit fields of one word: unpack unsigned (n_verify may reach 65535)
   const int n = rq.nv & 0xffff, nver = (int)((uint32_t)rq.nv >> 16), L = rq.ctx, T = L + n;
   const int g = a.g;
@@ -875,19 +881,24 @@ __global__ __launch_bounds__(kThreads) void attn_persist_kernel(AttnArgs a, Plan
 }
 
 template <int D, typename Plan>
-hipError_t launch_impl(const AttnArgs& args, const Plan& plan, hipStream_t stream) {
-  if (plan.persist_grid > 0) {
-    hipLaunchKernelGGL((attn_persist_kernel<D, Plan>), dim3(plan.persist_grid), dim3(kThreads), 0, stream, args,
-                       plan);
-    return hipGetLastError();
-  }
+hipError_t launch_main(const AttnArgs& args, const Plan& plan, hipStream_t stream) {
   if (plan.narrow)
     hipLaunchKernelGGL((attn_fwd_kernel<D, kNarrowWaves, Plan>), dim3(plan.grid_items),
                        dim3(threads_of(kNarrowWaves)), 0, stream, args, plan);
   else
     hipLaunchKernelGGL((attn_fwd_kernel<D, kWaves, Plan>), dim3(plan.grid_items), dim3(kThreads), 0, stream, args,
                        plan);
-  hipError_t e = hipGetLastError();
+  return hipGetLastError();
+}
+
+template <int D, typename Plan>
+hipError_t launch_impl(const AttnArgs& args, const Plan& plan, hipStream_t stream) {
+  if (plan.persist_grid > 0) {
+    hipLaunchKernelGGL((attn_persist_kernel<D, Plan>), dim3(plan.persist_grid), dim3(kThreads), 0, stream, args,
+                       plan);
+    return hipGetLastError();
+  }
+  hipError_t e = launch_main<D>(args, plan, stream);
   if (e != hipSuccess) return e;
   if (plan.total_comb > 0) {
     if (plan.max_chunks > 8 && plan.grid_comb <= 1024)  // long rows, and few enough items to be latency-bound
@@ -911,6 +922,12 @@ hipError_t launch_attention(const AttnArgs& args, const AttnPlanBr& plan, int he
                             hipStream_t stream) {
   if (head_dim == 128) return launch_impl<128>(args, plan, stream);
   return launch_impl<64>(args, plan, stream);
+}
+
+hipError_t launch_attention(const AttnArgs& args, const AttnPlanBrPacked& plan, int head_dim,
+                            hipStream_t stream) {
+  if (head_dim == 128) return launch_main<128>(args, plan, stream);
+  return launch_main<64>(args, plan, stream);
 }
 
 }  // namespace rg

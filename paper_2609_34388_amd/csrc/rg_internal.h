@@ -51,6 +51,46 @@ struct AttnReqBr : AttnReq {
 };
 constexpr int kMaxReqPerLaunchBr = 64;  // equals RG_BRANCH_MAX_REQS_PER_LAUNCH
 
+// The same in 7 words, for requests whose keys are one work item and whose
+// numbers fit the fields: two plans' requests then share one launch.
+struct AttnReqBrPacked {
+  uint32_t q_n;        // q_start (low 20 bits) | n << 20
+  uint32_t ctx_nv;     // ctx (low 20 bits) | n_verify << 20
+  int32_t page_start;
+  int32_t item_start;
+  uint32_t br[3];      // rows (bits 0-9) | prefix (10-19) | lead (20-23); bits 24-31: the
+                       // fields of `rep`: count, prefix step, index
+
+  bool pack(const AttnReqBr& r) {
+    const uint32_t n = r.nv & 0xffff, nv = (uint32_t)r.nv >> 16;
+    const uint32_t f[3] = {(uint32_t)r.rep & 0xffff, ((uint32_t)r.rep >> 16) & 0xfff, (uint32_t)r.rep >> 28};
+    if ((uint32_t)r.q_start >> 20 || (uint32_t)r.ctx >> 20 || n >> 12 || nv >> 12) return false;
+    q_n = (uint32_t)r.q_start | n << 20;
+    ctx_nv = (uint32_t)r.ctx | nv << 20;
+    page_start = r.page_start;
+    item_start = r.item_start;
+    for (int b = 0; b < 3; ++b) {
+      const uint32_t w = (uint32_t)r.br[b], rows = w & 0xffff, prefix = (w >> 16) & 0xfff, lead = w >> 28;
+      if (rows >> 10 || prefix >> 10 || f[b] >> 8) return false;
+      br[b] = rows | prefix << 10 | lead << 20 | f[b] << 24;
+    }
+    return true;
+  }
+  __host__ __device__ AttnReqBr unpack() const {
+    AttnReqBr r;
+    r.q_start = (int32_t)(q_n & 0xfffff);
+    r.ctx = (int32_t)(ctx_nv & 0xfffff);
+    r.nv = (int32_t)(q_n >> 20 | (ctx_nv >> 20) << 16);
+    r.page_start = page_start;
+    r.item_start = item_start;
+    r.part_start = r.comb_start = 0;
+    for (int b = 0; b < 3; ++b)
+      r.br[b] = (int32_t)((br[b] & 0x3ff) | ((br[b] >> 10) & 0x3ff) << 16 | ((br[b] >> 20) & 0xf) << 28);
+    r.rep = (int32_t)(br[0] >> 24 | (br[1] >> 24) << 16 | (br[2] >> 24) << 28);
+    return r;
+  }
+};
+
 template <typename Req, int MaxReq>
 struct AttnPlanT {
   int32_t num_req;         // requests in this launch
@@ -68,8 +108,10 @@ struct AttnPlanT {
 };
 using AttnPlan = AttnPlanT<AttnReq, kMaxReqPerLaunch>;
 using AttnPlanBr = AttnPlanT<AttnReqBr, kMaxReqPerLaunchBr>;
+using AttnPlanBrPacked = AttnPlanT<AttnReqBrPacked, 2 * kMaxReqPerLaunchBr>;
 static_assert(sizeof(AttnPlan) <= 3700, "attention plan must fit the kernel argument block");
 static_assert(sizeof(AttnPlanBr) <= 3700, "attention plan must fit the kernel argument block");
+static_assert(sizeof(AttnPlanBrPacked) <= 3700, "attention plan must fit the kernel argument block");
 
 struct AttnArgs {
   const uint16_t* q;
@@ -94,6 +136,8 @@ struct AttnArgs {
 hipError_t launch_attention(const AttnArgs& args, const AttnPlan& plan, int head_dim,
                             hipStream_t stream);
 hipError_t launch_attention(const AttnArgs& args, const AttnPlanBr& plan, int head_dim,
+                            hipStream_t stream);
+hipError_t launch_attention(const AttnArgs& args, const AttnPlanBrPacked& plan, int head_dim,
                             hipStream_t stream);
 
 // Logit-row reductions (logits.hip).

@@ -107,6 +107,38 @@ def test_multibranch_attention_matches_oracle(name):
     _check(out, lse, _reference(lay, inp, branches))
 
 
+@pytest.mark.parametrize("R,special", [
+    (65, "family255"), (128, "rows1023"), (129, None), (100, "empty"),  # two plans in one launch
+    (66, "family256"), (66, "rows1024"), (70, "prefix1024"),            # beyond a packed field: two launches
+])
+def test_more_requests_than_one_plan(R, special):
+    """More than 64 branched requests, on sampled requests against the oracle:
+    at the edges of what two plans packed into one launch can hold, and past them."""
+    rng = np.random.default_rng(R)
+    ctx = [int(x) for x in rng.integers(0, 200, R)]
+    nv = [int(x) for x in rng.integers(1, 8, R)]
+    branches = [[(v // 2, 1, 3), (v, 0, 4)] if i % 3 else [(v, 0, 5)] for i, v in enumerate(nv)]
+    at = 7
+    if special == "family255" or special == "family256":
+        k = int(special[6:])
+        nv[at], branches[at] = k - 1, [(a, 0, 1) for a in range(k)]
+    elif special == "rows1023" or special == "rows1024":
+        k = int(special[4:])
+        branches[at] = [(1, 1, k - 6), (0, 15, 2 * 16), (nv[at], 0, k)]
+    elif special == "prefix1024":
+        nv[at], branches[at] = 1024, [(1024, 1, 3), (1023, 0, 2)]
+    elif special == "empty":
+        for i in (0, 50, R - 1):
+            ctx[i], nv[i], branches[i] = 0, 0, []
+    lay = _layout(ctx, nv, branches, hq=2, hkv=1, D=64, seed=R)
+    inp = W.make_attention_inputs(lay, DEV, poison=float("nan"))
+    out, lse = _run(lay, inp, branches)
+    sample = [0, 1, at, R // 2, 63, 64, R - 1]
+    ref = _reference(lay, inp, branches, requests=sample)
+    rows = np.concatenate([np.arange(lay.q_indptr[r], lay.q_indptr[r + 1]) for r in sample])
+    _check(out, lse, ref, rows)
+
+
 def _random_branch_case(i):
     """Seeded random batch i: per request up to three branches of any shape,
     or a regular family (equal rows and lead, prefixes growing by a step),
