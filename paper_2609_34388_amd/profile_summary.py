@@ -118,7 +118,7 @@ def traffic_md(out: str, wl: str) -> str:
         fv, wv = statistics.mean(fetch[k]), statistics.mean(write.get(k, [0.0]))
         by = (fv * ff + wv * wf) * 1024
         lines.append(f"| {k} | {fv:.1f} | {wv:.1f} | {by / 1e6:.3f} MB |")
-        if k.startswith("attn_fwd_kernel<128, AttnPlanT<AttnReq, 128>") or k.startswith("attn_combine_kernel<128"):
+        if (k.startswith("attn_fwd_kernel<128") and "AttnPlanT<AttnReq, 128>" in k) or k.startswith("attn_combine_kernel<128"):
             if "AttnReqBr" not in k:
                 attn_bytes += by
     alg = b["attention"]["bytes"]
