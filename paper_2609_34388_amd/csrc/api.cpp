@@ -166,7 +166,8 @@ int choose_chunk(const std::vector<int64_t>& pair_keys, int hkv, int num_cus) {
   if (forced > 0) return (int)std::min<int64_t>(kMaxChunkKeys, round_up(forced, kKeyTile));
   const int64_t kCUs = std::max(1, num_cus);
   const int64_t kTwoRounds = 2 * kCUs;
-  const int64_t floor_keys = round_up(std::max(kKeyTile, env_int("RG_ATTN_MIN_CHUNK", 256)), kKeyTile);
+  const int64_t floor_keys =
+      std::min<int64_t>(kMaxChunkKeys, round_up(std::max(kKeyTile, env_int("RG_ATTN_MIN_CHUNK", 256)), kKeyTile));
   int64_t total = 0, longest = 0;
   for (int64_t t : pair_keys) {
     total += t * hkv;
@@ -252,7 +253,8 @@ int choose_run(const std::vector<PairLoad>& pairs, int hkv, int num_cus, int chu
     extra = std::max(extra, (double)(p.keys - run) * p.weight);
   }
   if (item > 1.35 * load * hkv / cus + 512.0) return chunk;
-  return (int)std::min<int64_t>(kMaxChunkKeys, extra <= 192.0 ? round_up(longest, kKeyTile) : run);
+  // never below the chunk, whose split sizes the workspace
+  return (int)std::max<int64_t>(chunk, std::min<int64_t>(kMaxChunkKeys, extra <= 192.0 ? round_up(longest, kKeyTile) : run));
 }
 
 // Whether a call's items, of at most `run` keys, run in narrow work groups (4
@@ -392,6 +394,7 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
         comb += hkv * ((M + 31) / 32) * (L->head_dim * 4 / comb_rows);  // slices of a tile's 4 D rows
       }
       if (plan_items > INT32_MAX / 2 || plan_part > INT32_MAX / 2) return RG_ERR_UNSUPPORTED;
+      if (part > plan_part) return RG_ERR_WORKSPACE;  // run >= chunk: the partials fit the workspace
     }
     p.req[cnt].item_start = (int32_t)items;
     p.req[cnt].part_start = (int32_t)part;

@@ -49,3 +49,20 @@ def test_chunk_is_shortest_fitting_two_rounds(spec, seed, nreq):
     else:
         assert 256 < chunk <= hi and chunk % 128 == 0
         assert _items(lay, chunk, g, hkv) <= ROUND2 < _items(lay, chunk - 128, g, hkv)
+
+
+@pytest.mark.parametrize("floor", [256, 65536, 65664, 131072, 2**31 - 1])
+def test_chunk_never_exceeds_the_longest_item(monkeypatch, floor):
+    """RG_ATTN_MIN_CHUNK raises the shortest chunk up to 65536 keys, the most a
+    work item takes: the workspace then holds the partials of items that long."""
+    monkeypatch.setenv("RG_ATTN_MIN_CHUNK", str(floor))
+    R, ctx, n, hq, hkv = 16, 200000, 32, 32, 8
+    pages = -(-(ctx + n) // 16)
+    l = _L(R=R, hq=hq, hkv=hkv, D=128, num_pages=pages * R, ctx=[ctx] * R, nv=[16] * R, n=[n] * R,
+           pages=[pages] * R)
+    info = _plan(l)
+    chunk = info.chunk_keys
+    assert chunk % 128 == 0 and 256 <= chunk <= 65536
+    need = R * hkv * -(-(ctx + n) // 65536) * n * (hq // hkv)  # partial columns at the longest item
+    assert info.partial_columns >= need
+    assert info.workspace_bytes >= need * (128 * 2 + 8)
