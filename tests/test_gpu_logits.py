@@ -334,3 +334,56 @@ def test_rows_at_any_two_byte_place(vocab):
         torch.cuda.synchronize()
         check_verify(dense, rp.cpu().numpy(), tok, res)
         check_draft(dense, run_draft(logits))
+
+
+@pytest.mark.parametrize("requests", [(1 << 23) - 8, (1 << 23) - 1, 1 << 23, (1 << 24) - 1, (1 << 24) + 9])
+def test_requests_around_the_threads_of_a_grid(requests):
+    """Requests whose finalize work groups reach and pass the 2^32 threads of
+    one launch, all but seven empty: every request gets its own result."""
+    owners = [0, 1, 4000, requests // 2 - 1, requests // 2, requests - 2, requests - 1]
+    counts = torch.zeros(requests, dtype=torch.int32, device=DEV)
+    counts[owners] = torch.tensor([2, 1, 3, 1, 2, 3, 2], dtype=torch.int32, device=DEV)
+    rows, vocab = 14, 96
+    rp = torch.zeros(requests + 1, dtype=torch.int32, device=DEV)
+    rp[1:] = counts.cumsum(0)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    logits = torch.randn(rows, vocab, generator=g, device=DEV).to(torch.bfloat16)
+    tok = torch.argmax(logits.float(), dim=1).to(torch.int32)
+    tok[[2, 8]] += 1
+    ref = oracle.oracle_accept(W.bf16_bits(logits), np.concatenate([[0], np.cumsum([2, 1, 3, 1, 2, 3, 2])]),
+                               tok.cpu().numpy())
+    for both in (False, True):
+        out = dict(accept_len=torch.full((requests,), -7, dtype=torch.int32, device=DEV),
+                   next_token=torch.full((requests,), -7, dtype=torch.int32, device=DEV))
+        if both:
+            draft = torch.randn(1030, vocab, generator=g, device=DEV).to(torch.bfloat16)
+            res, drafted = binding.verify_and_confidence(logits, rp, tok, draft, out_verify=out)
+            check_draft(draft, drafted)
+        else:
+            res = binding.verify_accept(logits, rp, tok, out=out)
+        empty = counts == 0
+        assert int((res["accept_len"][empty] != 0).sum()) == 0 and int((res["next_token"][empty] != -1).sum()) == 0
+        np.testing.assert_array_equal(res["accept_len"][owners].cpu().numpy(), ref["accept_len"])
+        np.testing.assert_array_equal(res["next_token"][owners].cpu().numpy(), ref["next_token"])
+        rel_ok(res["accept_entropy"][owners].cpu().numpy(), ref["accept_entropy"], floor=1e-30)
+
+
+@pytest.mark.parametrize("rows", [(1 << 24) - 8, (1 << 24) + 17])
+def test_rows_around_the_threads_of_a_grid(rows):
+    """Rows of two entries whose work groups reach and pass the 2^32 threads of
+    one launch: indices and token counts of every row, alone and in a round."""
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    logits = torch.randint(-8, 8, (rows, 2), generator=g, device=DEV).to(torch.bfloat16)
+    want = (logits[:, 1] > logits[:, 0]).to(torch.int32)
+    ones = lambda: torch.full((rows,), -7, dtype=torch.int32, device=DEV)
+    rp = torch.tensor([0, rows - 5, rows], dtype=torch.int32, device=DEV)
+    tok = want.clone()
+    tok[rows - 3] = 1 - tok[rows - 3]
+    v = binding.verify_accept(logits, rp, tok, want_entropy=False, out=dict(row_argmax=ones()))
+    assert torch.equal(v["row_argmax"], want) and v["accept_len"].tolist() == [rows - 5, 2]
+    d = binding.draft_confidence(logits, want_margin=False, want_entropy=False, out=dict(top1=ones(), top2=ones()))
+    assert torch.equal(d["top1"], want) and torch.equal(d["top2"], 1 - want)
+    few = logits[:40]
+    v, d = binding.verify_and_confidence(few, torch.tensor([0, 40], dtype=torch.int32, device=DEV), want[:40], logits,
+                                         out_draft=dict(top1=ones(), top2=ones()))
+    assert torch.equal(v["row_argmax"], want[:40]) and torch.equal(d["top1"], want) and torch.equal(d["top2"], 1 - want)
