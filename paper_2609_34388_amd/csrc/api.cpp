@@ -661,7 +661,6 @@ rg_status make_verify_args(const uint16_t* logits, int64_t row_stride, int32_t v
   a.row_entropy = row_entropy;
   a.accept_entropy = accept_entropy;
   a.chunk_st = static_cast<float4*>(ws);
-  a.grid_rows = (int32_t)round_up((int64_t)total_rows * a.nchunk, 8);
   return RG_OK;
 }
 
@@ -691,7 +690,6 @@ rg_status make_draft_args(const uint16_t* logits, int64_t row_stride, int32_t vo
   a.chunk_a = reinterpret_cast<float4*>(w);
   if (w != nullptr) w += align256((size_t)total_rows * a.nchunk * 16);
   a.chunk_b = reinterpret_cast<float2*>(w);
-  a.grid_rows = (int32_t)round_up((int64_t)total_rows * a.nchunk, 8);
   return RG_OK;
 }
 

@@ -471,10 +471,9 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, int item, Chunk
   if (threadIdx.x == 0) a.chunk_st[(size_t)row * a.nchunk + c] = make_float4(m, __int_as_float(i1), z, s);
 }
 
-// The grid of this launch is items first .. first + gridDim.x - 1 (see sliced).
-__global__ __launch_bounds__(kLogitThreads) void verify_rows_kernel(VerifyArgs a, int32_t first, int32_t grid) {
+__global__ __launch_bounds__(kLogitThreads) void verify_rows_kernel(VerifyArgs a) {
   __shared__ ChunkRed red;
-  const int item = first + xcd_item(grid);
+  const int item = a.first + xcd_item(a.grid);
   if (item < a.rows * a.nchunk) verify_rows(a, item, red);
 }
 
@@ -552,9 +551,9 @@ __device__ __forceinline__ void verify_finalize(const VerifyArgs& a, int r, Fina
   }
 }
 
-__global__ __launch_bounds__(kFinalizeThreads) void verify_finalize_kernel(VerifyArgs a, int32_t first) {
+__global__ __launch_bounds__(kFinalizeThreads) void verify_finalize_kernel(VerifyArgs a) {
   __shared__ FinalizeLds lds;
-  verify_finalize(a, first + (int)blockIdx.x, lds);
+  verify_finalize(a, a.first + (int)blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -572,9 +571,9 @@ __device__ __forceinline__ void draft_rows(const DraftArgs& a, int item, ChunkRe
   }
 }
 
-__global__ __launch_bounds__(kLogitThreads) void draft_rows_kernel(DraftArgs a, int32_t first, int32_t grid) {
+__global__ __launch_bounds__(kLogitThreads) void draft_rows_kernel(DraftArgs a) {
   __shared__ ChunkRed red;
-  const int item = first + xcd_item(grid);
+  const int item = a.first + xcd_item(a.grid);
   if (item < a.rows * a.nchunk) draft_rows(a, item, red);
 }
 
@@ -601,37 +600,42 @@ __device__ __forceinline__ void draft_finalize(const DraftArgs& a, int blk) {
   }
 }
 
-__global__ __launch_bounds__(kFinalizeThreads) void draft_finalize_kernel(DraftArgs a, int32_t first) {
-  draft_finalize(a, first + (int)blockIdx.x);
+__global__ __launch_bounds__(kFinalizeThreads) void draft_finalize_kernel(DraftArgs a) {
+  draft_finalize(a, a.first + (int)blockIdx.x);
 }
 
 // Both passes of one round in two launches: the row items of the verify rows
-// and of the draft rows share one grid, and so do the two finalize steps.
-__global__ __launch_bounds__(kLogitThreads) void round_rows_kernel(VerifyArgs v, DraftArgs d, int32_t first, int32_t grid) {
+// and of the draft rows share one grid, and so do the two finalize steps (its
+// first and grid are those of `v`).
+__global__ __launch_bounds__(kLogitThreads) void round_rows_kernel(VerifyArgs v, DraftArgs d) {
   __shared__ ChunkRed red;
-  const int item = first + xcd_item(grid);
+  const int item = v.first + xcd_item(v.grid);
   const int nv = v.rows * v.nchunk;
   if (item < nv) verify_rows(v, item, red);
   else if (item - nv < d.rows * d.nchunk) draft_rows(d, item - nv, red);
 }
 
-__global__ __launch_bounds__(kFinalizeThreads) void round_finalize_kernel(VerifyArgs v, DraftArgs d, uint32_t first) {
+__global__ __launch_bounds__(kFinalizeThreads) void round_finalize_kernel(VerifyArgs v, DraftArgs d) {
   __shared__ FinalizeLds lds;
-  const uint32_t b = first + blockIdx.x;
+  const uint32_t b = (uint32_t)v.first + blockIdx.x;
   if (b < (uint32_t)v.num_req) verify_finalize(v, (int)b, lds);
   else draft_finalize(d, (int)(b - (uint32_t)v.num_req));
 }
 
-// Calls launch(first, groups) for consecutive slices of `groups` work groups
-// of `threads` threads.  A launch holds fewer than 2^32 threads: at more its
-// grid wraps, and the rest of the work is left out with or without an error.
-// One slice up to 2^23 - 8 requests or 2^24 - 8 row chunks.  Slices are whole
-// multiples of 8 groups (xcd_item).
-template <typename Launch>
-hipError_t sliced(int64_t groups, int threads, Launch launch) {
+// Calls launch(args) for consecutive slices of `groups` work groups of
+// `threads` threads, args.first and args.grid telling the slice.  A launch
+// holds fewer than 2^32 threads: at more its grid wraps, and the rest of the
+// work is left out with or without an error.  One slice up to 2^23 - 8
+// requests or 2^24 - 8 row chunks.  Slices are whole multiples of 8 groups
+// (xcd_item).  The slice travels in the argument structs' padding: as two
+// more kernel arguments it cost 1 % of a pass over 2000 rows of 128256.
+template <typename Args, typename Launch>
+hipError_t sliced(Args args, int64_t groups, int threads, Launch launch) {
   const int64_t most = ((int64_t(1) << 32) - 1) / threads / 8 * 8;
   for (int64_t first = 0; first < groups; first += most) {
-    launch(first, (int32_t)std::min(most, groups - first));
+    args.first = (int32_t)(uint32_t)first;
+    args.grid = (int32_t)std::min(most, groups - first);
+    launch(args);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -678,35 +682,36 @@ hipError_t noalloc_scratch(void** ptr) {
 }
 
 hipError_t launch_verify(const VerifyArgs& a, hipStream_t stream) {
-  const hipError_t e = sliced(a.grid_rows, kLogitThreads, [&](int64_t first, int32_t grid) {
-    hipLaunchKernelGGL(verify_rows_kernel, dim3(grid), dim3(kLogitThreads), 0, stream, a, (int32_t)first, grid);
+  const int64_t items = (int64_t)a.rows * a.nchunk;
+  const hipError_t e = sliced(a, (items + 7) / 8 * 8, kLogitThreads, [&](const VerifyArgs& s) {
+    hipLaunchKernelGGL(verify_rows_kernel, dim3(s.grid), dim3(kLogitThreads), 0, stream, s);
   });
   if (e != hipSuccess) return e;
-  return sliced(a.num_req, kFinalizeThreads, [&](int64_t first, int32_t grid) {
-    hipLaunchKernelGGL(verify_finalize_kernel, dim3(grid), dim3(kFinalizeThreads), 0, stream, a, (int32_t)first);
+  return sliced(a, a.num_req, kFinalizeThreads, [&](const VerifyArgs& s) {
+    hipLaunchKernelGGL(verify_finalize_kernel, dim3(s.grid), dim3(kFinalizeThreads), 0, stream, s);
   });
 }
 
 hipError_t launch_draft(const DraftArgs& a, hipStream_t stream) {
-  if (a.grid_rows == 0) return hipSuccess;
-  const hipError_t e = sliced(a.grid_rows, kLogitThreads, [&](int64_t first, int32_t grid) {
-    hipLaunchKernelGGL(draft_rows_kernel, dim3(grid), dim3(kLogitThreads), 0, stream, a, (int32_t)first, grid);
+  const int64_t items = (int64_t)a.rows * a.nchunk;
+  const hipError_t e = sliced(a, (items + 7) / 8 * 8, kLogitThreads, [&](const DraftArgs& s) {
+    hipLaunchKernelGGL(draft_rows_kernel, dim3(s.grid), dim3(kLogitThreads), 0, stream, s);
   });
   if (e != hipSuccess) return e;
-  return sliced(draft_finalize_groups(a), kFinalizeThreads, [&](int64_t first, int32_t grid) {
-    hipLaunchKernelGGL(draft_finalize_kernel, dim3(grid), dim3(kFinalizeThreads), 0, stream, a, (int32_t)first);
+  return sliced(a, draft_finalize_groups(a), kFinalizeThreads, [&](const DraftArgs& s) {
+    hipLaunchKernelGGL(draft_finalize_kernel, dim3(s.grid), dim3(kFinalizeThreads), 0, stream, s);
   });
 }
 
 hipError_t launch_round(const VerifyArgs& v, const DraftArgs& d, hipStream_t stream) {
   const int64_t items = (int64_t)v.rows * v.nchunk + (int64_t)d.rows * d.nchunk;
-  const hipError_t e = sliced((items + 7) / 8 * 8, kLogitThreads, [&](int64_t first, int32_t grid) {
-    hipLaunchKernelGGL(round_rows_kernel, dim3(grid), dim3(kLogitThreads), 0, stream, v, d, (int32_t)first, grid);
+  const hipError_t e = sliced(v, (items + 7) / 8 * 8, kLogitThreads, [&](const VerifyArgs& s) {
+    hipLaunchKernelGGL(round_rows_kernel, dim3(s.grid), dim3(kLogitThreads), 0, stream, s, d);
   });
   if (e != hipSuccess) return e;
   const int64_t groups = (int64_t)v.num_req + (d.rows > 0 ? draft_finalize_groups(d) : 0);
-  return sliced(groups, kFinalizeThreads, [&](int64_t first, int32_t grid) {
-    hipLaunchKernelGGL(round_finalize_kernel, dim3(grid), dim3(kFinalizeThreads), 0, stream, v, d, (uint32_t)first);
+  return sliced(v, groups, kFinalizeThreads, [&](const VerifyArgs& s) {
+    hipLaunchKernelGGL(round_finalize_kernel, dim3(s.grid), dim3(kFinalizeThreads), 0, stream, s, d);
   });
 }
 

@@ -158,7 +158,7 @@ struct VerifyArgs {
   float* row_entropy;
   float* accept_entropy;
   float4* chunk_st;    // workspace [rows * nchunk] (max, bits(argmax), Z', S)
-  int32_t grid_rows;   // row work groups (rows * nchunk rounded up to 8)
+  int32_t grid, first;  // work groups of this launch, and the first one's item (set by the launch)
 };
 
 struct DraftArgs {
@@ -175,7 +175,7 @@ struct DraftArgs {
   float* entropy;
   float4* chunk_a;       // workspace [rows * nchunk] (max, bits(i1), v2, bits(i2))
   float2* chunk_b;       // [rows * nchunk] (Z', S)
-  int32_t grid_rows;
+  int32_t grid, first;   // as in VerifyArgs
 };
 
 inline int32_t logit_chunks(int32_t vocab) { return (vocab + kLogitChunk - 1) / kLogitChunk; }
