@@ -643,8 +643,9 @@ def measure_workload(name, seed, dev, steps, warmup, copies_arg=0, detail=False)
     logit_bytes = work["verify_bytes"] + work["draft_bytes"]
     gbps = lambda b, ms: b / (ms * 1e-3) / 1e9
     plan = binding.attention_plan(layouts[0])
+    launches = binding.attention_launches(layouts[0])
     res = dict(
-        lay=lay, work=work, step_bytes=step_bytes, copies=copies, per_copy=per_copy, plan=plan,
+        lay=lay, work=work, step_bytes=step_bytes, copies=copies, per_copy=per_copy, launches=launches,
         ms_step=ms_step, attn_ms=attn_ms, round_ms=round_ms, step_med=step_med, attn_med=attn_med,
         summary={"step_us": round(ms_step * 1e3, 3), "step_us_event_median": round(step_med * 1e3, 3),
                  "value": round(100.0 * gbps(step_bytes, ms_step) / HBM_PEAK_GBPS, 3),
@@ -738,7 +739,7 @@ def main(argv=None):
     t_start = time.perf_counter()
 
     m = measure_workload(args.workload, args.seed, dev, args.steps, args.warmup, args.copies, detail=True)
-    lay, work, plan = m["lay"], m["work"], m["plan"]
+    lay, work, launches = m["lay"], m["work"], m["launches"]
     s = lay.spec
     ms_step, attn_ms, round_ms = m["ms_step"], m["attn_ms"], m["round_ms"]
     ver_ms, dr_ms = m["ver_ms"], m["dr_ms"]
@@ -747,7 +748,7 @@ def main(argv=None):
     attn_gbps = work["attn_bytes"] / (attn_ms * 1e-3) / 1e9
     attn_tflops = work["attn_flops"] / (attn_ms * 1e-3) / 1e12
     traffic = measured_traffic(args.workload) if args.seed == 0 else None
-    kernels = "attn_fwd_kernel + attn_combine_kernel" if plan["split_requests"] else "attn_fwd_kernel"
+    kernels = "attn_fwd_kernel + attn_combine_kernel" if launches["merge_launches"] else "attn_fwd_kernel"
 
     result = {
         "metric": "draft-verify attention TFLOP/s + logits GB/s, % of MI355X roofline, 1 GPU",
@@ -770,8 +771,8 @@ def main(argv=None):
                    "kv_heads": s.num_kv_heads, "head_dim": s.head_dim, "page_size": 16,
                    "context_tokens": int(lay.ctx_len.sum()), "verify_rows": int(lay.n_verify.sum()),
                    "draft_rows": int(lay.n_draft.sum()), "vocab": s.vocab, "seed": args.seed,
-                   "input_copies_rotated": m["copies"], "attn_chunk_keys": plan["chunk_keys"],
-                   "attn_work_items": plan["work_items"]},
+                   "input_copies_rotated": m["copies"], "attn_chunk_keys": launches["run_keys"],
+                   "attn_work_items": launches["work_items"], "attn_narrow_groups": bool(launches["narrow"])},
         "step_ms_event_median": round(m["step_med"], 5),
         "attention": {"ms": round(attn_ms, 5), "ms_event_median": round(m["attn_med"], 5),
                       "tflops": round(attn_tflops, 3), "gbps": round(attn_gbps, 1),

@@ -183,17 +183,17 @@ rg_status rg_draft_verify_attention(const rg_attn_layout* layout, const uint16_t
  */
 rg_status rg_draft_verify_attention_check(void* ws, size_t ws_bytes, void* stream);
 
-/* Planning summary of an attention call (host only, no GPU work): used by
- * tests and tools to inspect how the batch is split.  It describes the finest
- * split a call uses, which sizes the workspace; a two-launch call may give a
- * work group a longer run of keys than chunk_keys, where one round of work
- * groups is faster than two, and then writes fewer partials. */
+/* Planning summary of an attention call (host only, no GPU work): how the
+ * batch is split for the workspace.  That is the finest split a call uses: a
+ * two-launch call may give a work group a longer run of keys than chunk_keys,
+ * where one round of work groups is faster than two, and then writes fewer
+ * partials.  What a call launches: rg_attention_launches. */
 typedef struct rg_attn_plan_info {
   int32_t num_launches;     /* launches of the main kernel                   */
   int32_t chunk_keys;       /* keys per KV chunk                             */
   int64_t work_items;       /* (request, kv head, column group, chunk) items */
   int64_t split_requests;   /* requests whose keys span more than one chunk  */
-  int64_t partial_columns;  /* partial rows written to the workspace         */
+  int64_t partial_columns;  /* partial rows of this split                    */
   int64_t workspace_bytes;
   int32_t persistent_launches; /* launches run as one work-queue launch      */
   int32_t sync_words;       /* int32 synchronisation words at sync_offset    */
@@ -203,6 +203,25 @@ typedef struct rg_attn_plan_info {
                                expected; see rg_draft_verify_attention_check) */
 } rg_attn_plan_info;
 rg_status rg_draft_verify_attention_plan(const rg_attn_layout* layout, rg_attn_plan_info* info);
+
+/* The launches of rg_draft_verify_attention (branches = NULL) or
+ * rg_multibranch_attention with these arguments (host only, no GPU work). */
+struct rg_branch_layout;
+typedef struct rg_attn_launch_info {
+  int32_t launches;         /* launches of the main kernel                   */
+  int32_t joined_launches;  /* of them, launches of two plans                */
+  int32_t merge_launches;   /* launches of the merge kernel                  */
+  int32_t run_keys;         /* keys per work item at most, >= chunk_keys     */
+  int32_t narrow;           /* 1: work groups of 128 columns, 0: of 256      */
+  int32_t reserved;
+  int64_t work_items;       /* (request, kv head, column group, run) items   */
+  int64_t split_requests;   /* requests whose keys span more than one item   */
+  int64_t partial_columns;  /* partial rows written to the workspace         */
+  int64_t max_launch_partial_columns;  /* the most of one launch: they share
+                                          the workspace                      */
+} rg_attn_launch_info;
+rg_status rg_attention_launches(const rg_attn_layout* layout, const struct rg_branch_layout* branches,
+                                rg_attn_launch_info* info);
 
 /*
  * Greedy verification (Sec. 3.1; greedy decoding as in Sec. 6.1).

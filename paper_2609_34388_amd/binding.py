@@ -62,9 +62,16 @@ class AttnPlanInfo(ctypes.Structure):
                 ("sync_offset", ctypes.c_int64)]
 
 
+class AttnLaunchInfo(ctypes.Structure):
+    _fields_ = [("launches", ctypes.c_int32), ("joined_launches", ctypes.c_int32),
+                ("merge_launches", ctypes.c_int32), ("run_keys", ctypes.c_int32), ("narrow", ctypes.c_int32),
+                ("reserved", ctypes.c_int32), ("work_items", ctypes.c_int64), ("split_requests", ctypes.c_int64),
+                ("partial_columns", ctypes.c_int64), ("max_launch_partial_columns", ctypes.c_int64)]
+
+
 EXPORTS = ("rg_abi_version", "rg_status_string", "rg_draft_verify_attention_workspace",
            "rg_draft_verify_attention", "rg_draft_verify_attention_plan", "rg_draft_verify_attention_check",
-           "rg_verify_accept_workspace", "rg_verify_accept", "rg_draft_confidence_workspace",
+           "rg_attention_launches", "rg_verify_accept_workspace", "rg_verify_accept", "rg_draft_confidence_workspace",
            "rg_draft_confidence", "rg_verify_and_confidence_workspace", "rg_verify_and_confidence",
            "rg_verify_and_confidence_noalloc",
            "rg_multibranch_attention_workspace", "rg_multibranch_attention", "rg_plan_branches",
@@ -86,6 +93,8 @@ def _lib():
         "rg_status_string": (ctypes.c_char_p, [I32]),
         "rg_draft_verify_attention_workspace": (I32, [ctypes.POINTER(AttnLayout), ctypes.POINTER(SZ)]),
         "rg_draft_verify_attention_plan": (I32, [ctypes.POINTER(AttnLayout), ctypes.POINTER(AttnPlanInfo)]),
+        "rg_attention_launches": (I32, [ctypes.POINTER(AttnLayout), ctypes.POINTER(BranchLayout),
+                                        ctypes.POINTER(AttnLaunchInfo)]),
         "rg_draft_verify_attention": (I32, [ctypes.POINTER(AttnLayout), P, P, P, P, P, P, SZ, P]),
         "rg_draft_verify_attention_check": (I32, [P, SZ, P]),
         "rg_verify_accept_workspace": (I32, [I32, I32, I32, ctypes.POINTER(SZ)]),
@@ -222,6 +231,15 @@ def attention_plan(layout: _Layout) -> Dict[str, int]:
     _check(_lib().rg_draft_verify_attention_plan(ctypes.byref(layout.c), ctypes.byref(info)),
            "rg_draft_verify_attention_plan")
     return {f: int(getattr(info, f)) for f, _ in AttnPlanInfo._fields_}
+
+
+def attention_launches(layout: _Layout, branches: Optional["_Branches"] = None) -> Dict[str, int]:
+    """What draft_verify_attention (or, with branches, multibranch_attention)
+    launches for this layout."""
+    info = AttnLaunchInfo()
+    _check(_lib().rg_attention_launches(ctypes.byref(layout.c), ctypes.byref(branches.c) if branches else None,
+                                        ctypes.byref(info)), "rg_attention_launches")
+    return {f: int(getattr(info, f)) for f, _ in AttnLaunchInfo._fields_ if f != "reserved"}
 
 
 def draft_verify_attention(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tensor,

@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "rg_internal.h"
@@ -118,8 +119,10 @@ struct FullPlanT {
   std::vector<Plan> launches;
   int chunk = 0;      // the finest split: it sizes the workspace and orders one-launch calls
   int run = 0;        // keys per work item of the launches, >= chunk
+  bool narrow = false;  // narrow work groups
   int cols_per_group = 256;
   int64_t items = 0, split_requests = 0, max_partial_cols = 0, total_partial_cols = 0;
+  int64_t run_split_requests = 0, run_max_partial_cols = 0, run_partial_cols = 0;  // of the launches
   int64_t max_comb = 0;
   int persistent_launches = 0;
   size_t ws_bytes = 0;
@@ -322,9 +325,9 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
   }
   fp.chunk = choose_chunk(pair_keys, hkv, num_cus);
   fp.run = persist || env_int("RG_ATTN_CHUNK", 0) > 0 ? fp.chunk : choose_run(pairs, hkv, num_cus, fp.chunk);
-  const bool narrow = narrow_items(pairs, hkv, num_cus, L->head_dim, fp.run);
+  fp.narrow = narrow_items(pairs, hkv, num_cus, L->head_dim, fp.run);
   // One round of narrow items is two to a CU: requests just over the split stay whole.
-  if (narrow && fp.run == fp.chunk && !persist && env_int("RG_ATTN_CHUNK", 0) == 0)
+  if (fp.narrow && fp.run == fp.chunk && !persist && env_int("RG_ATTN_CHUNK", 0) == 0)
     fp.run = choose_run(pairs, hkv, 2 * num_cus, fp.chunk);
   // Costliest work items first: work groups are dispatched in item order, so
   // the long items start early and the short ones fill in at the end.  An
@@ -360,7 +363,7 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
     p.num_req = cnt;
     p.chunk = fp.run;
     p.cols_per_group = fp.cols_per_group;
-    p.narrow = narrow ? 1 : 0;
+    p.narrow = fp.narrow ? 1 : 0;
     int64_t items = 0, part = 0, comb = 0;    // of the launch
     int64_t plan_items = 0, plan_part = 0;    // at the workspace's split
     for (int k = 0; k < cnt; ++k) {
@@ -388,6 +391,7 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
         fp.split_requests += 1;
       }
       if (nch > 1) {
+        fp.run_split_requests += 1;
         p.max_chunks = std::max<int32_t>(p.max_chunks, (int32_t)nch);
         // partials are stored per 32-column tile, so columns round up to 32
         part += hkv * nch * round_up(M, 32);
@@ -410,6 +414,8 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
     fp.items += plan_items;
     fp.max_partial_cols = std::max(fp.max_partial_cols, plan_part);
     fp.total_partial_cols += plan_part;
+    fp.run_max_partial_cols = std::max(fp.run_max_partial_cols, part);
+    fp.run_partial_cols += part;
     fp.max_comb = std::max(fp.max_comb, comb);
     fp.launches.push_back(p);
   }
@@ -498,6 +504,25 @@ bool join_plans(const AttnPlanBr& a, const AttnPlanBr& b, AttnPlanBrPacked& p) {
   return true;
 }
 
+// Calls launch(plan) for every launch of a call, in order, until one returns
+// false: the launches' plans, or two of them joined.
+template <typename Plan, typename Launch>
+bool each_launch(const FullPlanT<Plan>& fp, Launch launch) {
+  for (size_t l = 0; l < fp.launches.size(); ++l) {
+    const Plan& p = fp.launches[l];
+    if constexpr (__is_same(Plan, AttnPlanBr)) {
+      AttnPlanBrPacked both;
+      if (l + 1 < fp.launches.size() && join_plans(p, fp.launches[l + 1], both)) {
+        if (!launch(both)) return false;
+        ++l;
+        continue;
+      }
+    }
+    if (p.total_items > 0 && !launch(p)) return false;
+  }
+  return true;
+}
+
 template <typename Plan>
 rg_status run_attention(const rg_attn_layout* layout, const FullPlanT<Plan>& fp, const uint16_t* q,
                         const uint16_t* k_cache, const uint16_t* v_cache, uint16_t* out, float* lse,
@@ -525,20 +550,26 @@ rg_status run_attention(const rg_attn_layout* layout, const FullPlanT<Plan>& fp,
   a.scale_log2 = a.sm_scale * 1.4426950408889634f;
   a.rescale_gap = 8.0f / a.scale_log2;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  for (size_t l = 0; l < fp.launches.size(); ++l) {
-    const Plan& p = fp.launches[l];
-    if constexpr (__is_same(Plan, AttnPlanBr)) {
-      AttnPlanBrPacked both;
-      if (l + 1 < fp.launches.size() && join_plans(p, fp.launches[l + 1], both)) {
-        if (launch_attention(a, both, layout->head_dim, s) != hipSuccess) return RG_ERR_HIP;
-        ++l;
-        continue;
-      }
-    }
-    if (p.total_items == 0) continue;
-    if (launch_attention(a, p, layout->head_dim, s) != hipSuccess) return RG_ERR_HIP;
-  }
-  return RG_OK;
+  const bool ok = each_launch(fp, [&](const auto& p) { return launch_attention(a, p, layout->head_dim, s) == hipSuccess; });
+  return ok ? RG_OK : RG_ERR_HIP;
+}
+
+// What a call of this plan launches.
+template <typename Plan>
+void launch_info(const FullPlanT<Plan>& fp, rg_attn_launch_info* info) {
+  std::memset(info, 0, sizeof(*info));
+  info->run_keys = fp.run;
+  info->narrow = fp.narrow ? 1 : 0;
+  info->split_requests = fp.run_split_requests;
+  info->partial_columns = fp.run_partial_cols;
+  info->max_launch_partial_columns = fp.run_max_partial_cols;
+  each_launch(fp, [&](const auto& p) {
+    info->launches += 1;
+    info->work_items += p.total_items;
+    if (__is_same(std::decay_t<decltype(p)>, AttnPlanBrPacked)) info->joined_launches += 1;
+    if (p.persist_grid == 0 && p.total_comb > 0) info->merge_launches += 1;
+    return true;
+  });
 }
 
 }  // namespace
@@ -586,6 +617,23 @@ rg_status rg_draft_verify_attention_plan(const rg_attn_layout* layout, rg_attn_p
   info->sync_words = fp.ws_bytes ? kSyncWords : 0;
   info->sync_offset = fp.ws_bytes ? (int64_t)fp.sync_offset : -1;
   return RG_OK;
+}
+
+rg_status rg_attention_launches(const rg_attn_layout* layout, const rg_branch_layout* branches,
+                                rg_attn_launch_info* info) {
+  if (info == nullptr) return RG_ERR_NULL;
+  rg_status st = validate_layout(layout);
+  if (st != RG_OK) return st;
+  if (branches == nullptr) {
+    FullPlan fp;
+    st = plan_plain(layout, fp, device_cus());
+    if (st == RG_OK) launch_info(fp, info);
+    return st;
+  }
+  FullPlanBr fp;
+  st = plan_branched(layout, branches, fp, device_cus());
+  if (st == RG_OK) launch_info(fp, info);
+  return st;
 }
 
 rg_status rg_draft_verify_attention(const rg_attn_layout* layout, const uint16_t* q,

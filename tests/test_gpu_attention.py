@@ -131,6 +131,11 @@ def test_narrow_and_full_work_groups(monkeypatch, D, g, full, chunk):
     lay = _custom(len(rows), [t - n for t, n in zip(total, rows)], nv, [n - v for n, v in zip(rows, nv)],
                   hq=2 * g, hkv=2, D=D, seed=D + g)
     inp = W.make_attention_inputs(lay, DEV, poison=float("nan"))
+    layout = binding.make_layout(inp["q"], inp["k_cache"], lay.q_indptr, lay.n_verify, lay.ctx_len, lay.page_indptr,
+                                 torch.as_tensor(lay.page_indices, device=DEV))
+    launches = binding.attention_launches(layout)
+    assert bool(launches["narrow"]) != full and launches["run_keys"] == (chunk or 256)
+    assert launches["split_requests"] == (5 if chunk else 2) + full
     out, lse = run(lay, inp)
     check(out, lse, reference(lay, inp))
 
@@ -349,25 +354,34 @@ def test_full_size_configs_sampled(name, samples):
         check(out[q0:q1], lse[q0:q1], ref)
 
 
-@pytest.mark.parametrize("case", [
-    dict(ctx=[1500] * 7, nv=[5] * 7, nd=[6] * 7),                              # one round, several chunks per request
-    dict(ctx=[300, 2400, 700], nv=[8] * 3, nd=[8] * 3, hq=32, hkv=8),          # one round, some requests whole
-    dict(ctx=[513, 520, 250, 300], nv=[4] * 4, nd=[4] * 4, hq=32, hkv=8),      # whole: little longer than a run
-    dict(ctx=[4000] + [150] * 15, nv=[3] * 16, nd=[5] * 16, hq=32, hkv=8),     # skewed: one request far longer
-    dict(ctx=[260] * 32, nv=[2] * 32, nd=[2] * 32, hq=32, hkv=8),              # 256 whole items: exactly one round
-    dict(ctx=[260] * 33, nv=[2] * 33, nd=[2] * 33, hq=32, hkv=8),              # 264: more than one
-    dict(ctx=[900, 40, 1300], nv=[20, 1, 9], nd=[60, 2, 70], hq=16, hkv=2),    # several column groups
-    dict(ctx=[1700, 90, 0, 800], nv=[7, 0, 0, 2], nd=[9, 3, 0, 5], D=64, hq=8, hkv=4),
+@pytest.mark.parametrize("case,longer,split,narrow", [
+    (dict(ctx=[1500] * 7, nv=[5] * 7, nd=[6] * 7), False, 7, True),                        # the chunk itself, several per request
+    (dict(ctx=[300, 2400, 700], nv=[8] * 3, nd=[8] * 3, hq=32, hkv=8), False, 3, True),    # uneven lengths
+    (dict(ctx=[513, 520, 250, 300], nv=[4] * 4, nd=[4] * 4, hq=32, hkv=8), False, 4, True),  # little longer than one or two
+    (dict(ctx=[4000] + [150] * 15, nv=[3] * 16, nd=[5] * 16, hq=32, hkv=8), False, 1, True),  # skewed: one request far longer
+    (dict(ctx=[260] * 32, nv=[2] * 32, nd=[2] * 32, hq=32, hkv=8), True, 0, True),         # 256 whole items: exactly one round
+    (dict(ctx=[260] * 33, nv=[2] * 33, nd=[2] * 33, hq=32, hkv=8), False, 0, True),        # 264: more than one
+    (dict(ctx=[900, 40, 1300], nv=[20, 1, 9], nd=[60, 2, 70], hq=16, hkv=2), False, 2, False),  # several column groups
+    (dict(ctx=[1700, 90, 0, 800], nv=[7, 0, 0, 2], nd=[9, 3, 0, 5], D=64, hq=8, hkv=4), False, 2, True),
+    (dict(ctx=[1500] * 20, nv=[5] * 20, nd=[6] * 20, hq=8, hkv=8), True, 0, True),         # one round, all whole
+    (dict(ctx=[3000] * 12, nv=[3] * 12, nd=[5] * 12, hq=8, hkv=8), True, 12, True),        # one round, all split
+    (dict(ctx=[3000] * 12, nv=[3] * 12, nd=[137] * 12, hq=8, hkv=8), True, 12, False),     # the same in full groups
+    (dict(ctx=[700, 3400, 90, 2100] * 3, nv=[20, 7, 9, 1] * 3, nd=[60, 2, 70, 3] * 3, hq=32, hkv=8), True, 6, False),
+    (dict(ctx=[2600] * 28 + [90], nv=[3] * 29, nd=[5] * 29, D=64, hq=8, hkv=8), True, 0, False),  # one round, long items
 ])
-def test_runs_of_one_round(case):
+def test_runs_of_one_round(case, longer, split, narrow):
     """Batches on either side of the rule that gives a work item more keys
-    than the workspace's split: the results, and that the call stays within
-    a workspace of the queried size."""
+    than the workspace's split (`longer`; then `split` requests still span
+    several items): the path taken, the results, and that the call stays
+    within a workspace of the queried size."""
     kw = {k: case[k] for k in ("hq", "hkv", "D") if k in case}
     lay = _custom(len(case["ctx"]), case["ctx"], case["nv"], case["nd"], **kw)
     inp = W.make_attention_inputs(lay, DEV, poison=float("nan"))
     layout = binding.make_layout(inp["q"], inp["k_cache"], lay.q_indptr, lay.n_verify, lay.ctx_len, lay.page_indptr,
                                  torch.as_tensor(lay.page_indices, device=DEV))
+    plan, launches = binding.attention_plan(layout), binding.attention_launches(layout)
+    assert (launches["run_keys"] > plan["chunk_keys"]) == longer
+    assert (launches["split_requests"], bool(launches["narrow"])) == (split, narrow)
     need = binding.attention_workspace_bytes(layout)
     buf = torch.zeros(need + 4096, dtype=torch.uint8, device=DEV)
     buf[need:] = 0xA5

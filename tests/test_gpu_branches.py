@@ -107,13 +107,18 @@ def test_multibranch_attention_matches_oracle(name):
     _check(out, lse, _reference(lay, inp, branches))
 
 
-@pytest.mark.parametrize("R,special", [
-    (65, "family255"), (128, "rows1023"), (129, None), (100, "empty"),  # two plans in one launch
-    (66, "family256"), (66, "rows1024"), (70, "prefix1024"),            # beyond a packed field: two launches
+@pytest.mark.parametrize("heads", [(2, 1, 64), (8, 2, 128)])
+@pytest.mark.parametrize("R,special,joined,narrow", [
+    (65, "family255", 1, False), (128, "rows1023", 1, False), (129, None, 1, True), (100, "empty", 1, True),
+    # beyond a packed field: two launches
+    (66, "family256", 0, False), (66, "rows1024", 0, False), (70, "prefix1024", 0, False),
 ])
-def test_more_requests_than_one_plan(R, special):
+def test_more_requests_than_one_plan(monkeypatch, heads, R, special, joined, narrow):
     """More than 64 branched requests, on sampled requests against the oracle:
-    at the edges of what two plans packed into one launch can hold, and past them."""
+    at the edges of what two plans packed into one launch can hold, and past
+    them, in narrow and in full work groups (whole requests: only those join)."""
+    if special and special != "empty":
+        monkeypatch.setenv("RG_ATTN_CHUNK", "4096")
     rng = np.random.default_rng(R)
     ctx = [int(x) for x in rng.integers(0, 200, R)]
     nv = [int(x) for x in rng.integers(1, 8, R)]
@@ -130,8 +135,14 @@ def test_more_requests_than_one_plan(R, special):
     elif special == "empty":
         for i in (0, 50, R - 1):
             ctx[i], nv[i], branches[i] = 0, 0, []
-    lay = _layout(ctx, nv, branches, hq=2, hkv=1, D=64, seed=R)
+    hq, hkv, D = heads
+    lay = _layout(ctx, nv, branches, hq=hq, hkv=hkv, D=D, seed=R)
     inp = W.make_attention_inputs(lay, DEV, poison=float("nan"))
+    L = binding.make_layout(inp["q"], inp["k_cache"], lay.q_indptr, lay.n_verify, lay.ctx_len, lay.page_indptr,
+                            torch.as_tensor(lay.page_indices, device=DEV))
+    launches = binding.attention_launches(L, binding.make_branches(*_branch_arrays(branches)))
+    assert (launches["joined_launches"], bool(launches["narrow"])) == (joined, narrow)
+    assert launches["split_requests"] == 0 and launches["launches"] == -(-R // 64) - joined
     out, lse = _run(lay, inp, branches)
     sample = [0, 1, at, R // 2, 63, 64, R - 1]
     ref = _reference(lay, inp, branches, requests=sample)
