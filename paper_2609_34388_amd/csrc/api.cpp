@@ -292,6 +292,11 @@ bool narrow_items(const std::vector<PairLoad>& pairs, int hkv, int num_cus, int 
   return run <= (tiles <= 2 ? 2432 : one_round ? 256 : 512);
 }
 
+int item_threads(bool narrow) { return narrow ? kFullThreads / 2 : kFullThreads; }
+
+// Whether a grid of this many work groups, rounded up to 8, is one launch.
+bool fits_launch(int64_t groups, int threads) { return round_up(groups, 8) * threads <= kMaxLaunchThreads; }
+
 // Launches with a split request run as the main kernel plus the combine
 // kernel, or, with RG_ATTN_PERSIST=1, as one work-queue launch (main items,
 // then the combine items; `num_cus` work groups at most).  The two launches
@@ -407,7 +412,9 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
     p.total_comb = (int32_t)comb;
     p.grid_items = (int32_t)round_up(items, 8);
     p.grid_comb = (int32_t)round_up(comb, 8);
-    if (persist && comb > 0 && comb <= kMaxSyncComb) {
+    if (!(persist && comb > 0 && comb <= kMaxSyncComb)) {
+      if (!fits_launch(items, item_threads(fp.narrow)) || !fits_launch(comb, kCombThreads)) return RG_ERR_UNSUPPORTED;
+    } else {
       p.persist_grid = (int32_t)round_up(std::min<int64_t>(items + comb, std::max(8, num_cus)), 8);
       fp.persistent_launches += 1;
     }
@@ -486,6 +493,7 @@ rg_status plan_branched(const rg_attn_layout* layout, const rg_branch_layout* br
 // 0.76 to 1.08x on those batches, since each launch starts a round of its own.
 bool join_plans(const AttnPlanBr& a, const AttnPlanBr& b, AttnPlanBrPacked& p) {
   if (a.total_comb > 0 || b.total_comb > 0 || a.total_items == 0 || b.total_items == 0) return false;
+  if (!fits_launch((int64_t)a.total_items + b.total_items, item_threads(a.narrow))) return false;
   std::memset(&p, 0, sizeof(p));
   p.num_req = a.num_req + b.num_req;
   p.chunk = a.chunk;

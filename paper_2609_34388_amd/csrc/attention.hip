@@ -139,6 +139,7 @@ constexpr int kWaves = 8;        // compute waves of a full work group (two per 
 constexpr int kNarrowWaves = 4;  // ... of a narrow one, 128 columns, two to a CU
 constexpr int threads_of(int waves) { return 64 * (waves + waves / 2); }  // with one copy wave per two
 constexpr int kThreads = threads_of(kWaves);
+static_assert(kThreads == kFullThreads && threads_of(kNarrowWaves) == kFullThreads / 2, "the host's launch limit");
 // Keys staged per LDS buffer of a work group of `waves` compute waves.
 constexpr int super_keys(int waves) { return 16 * waves; }
 constexpr int kKBufs = 2;    // K buffers: one computed, one being filled
@@ -666,6 +667,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
 // column group to pass the wait returns its two counters to zero for the
 // next call.
 constexpr int kCombRows = 128;         // 16-byte rows per item of the combine kernel
+static_assert(kCombRows == kCombThreads, "the host's launch limit");
 constexpr int kCombRowsPersist = 256;  // ... and of a combine item of the one-launch kernel
 constexpr int kCombPartsPersist = 3;   // 3 x 256 threads = the one-launch work group
 constexpr int kSpinLimit = 1 << 20;    // polls (each a device round trip, 1-2 us) before giving up

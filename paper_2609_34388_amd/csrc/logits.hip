@@ -623,15 +623,13 @@ __global__ __launch_bounds__(kFinalizeThreads) void round_finalize_kernel(Verify
 }
 
 // Calls launch(args) for consecutive slices of `groups` work groups of
-// `threads` threads, args.first and args.grid telling the slice.  A launch
-// holds fewer than 2^32 threads: at more its grid wraps, and the rest of the
-// work is left out with or without an error.  One slice up to 2^23 - 8
-// requests or 2^24 - 8 row chunks.  Slices are whole multiples of 8 groups
-// (xcd_item).  The slice travels in the argument structs' padding: as two
+// `threads` threads, args.first and args.grid telling the slice: one up to
+// 2^23 - 8 requests or 2^24 - 8 row chunks.  Slices are whole multiples of 8
+// groups (xcd_item).  The slice travels in the argument structs' padding: as two
 // more kernel arguments it cost 1 % of a pass over 2000 rows of 128256.
 template <typename Args, typename Launch>
 hipError_t sliced(Args args, int64_t groups, int threads, Launch launch) {
-  const int64_t most = ((int64_t(1) << 32) - 1) / threads / 8 * 8;
+  const int64_t most = kMaxLaunchThreads / threads / 8 * 8;
   for (int64_t first = 0; first < groups; first += most) {
     args.first = (int32_t)(uint32_t)first;
     args.grid = (int32_t)std::min(most, groups - first);

@@ -13,6 +13,11 @@ constexpr int kPageSize = 16;
 constexpr int kMaxReqPerLaunch = 128;  // equals RG_ATTN_MAX_REQS_PER_LAUNCH
 constexpr int kKeyTile = 128;          // keys per LDS buffer; chunks are multiples of it
 constexpr int kNarrowCols = 128;       // query columns of a narrow attention work group
+constexpr int kFullThreads = 768;      // threads of a full attention work group; a narrow one has half
+constexpr int kCombThreads = 128;      // ... of a merge work group at least
+// Threads of one launch at most: at 2^32 its grid wraps, and the rest of the
+// work is left out with or without an error.
+constexpr int64_t kMaxLaunchThreads = (int64_t(1) << 32) - 1;
 constexpr int kMaxChunkKeys = 1 << 16;  // keys per work item at most
 constexpr int kSyncHeader = 4;          // queue head, exit count, give-up flag, report word
 // Combine items of one launch the one-launch kernel can count (two counters

@@ -242,3 +242,20 @@ def test_query_rows_past_the_packed_field(monkeypatch, rows, joined):
     B = binding.make_branches(np.arange(R + 1), [0] * R, [0] * R, n)
     got = _launches(_batch([10] * R, n, hq=1, hkv=1), B)
     assert got.joined_launches == joined
+
+
+@pytest.mark.parametrize("n,hkv,joined", [(1, 87376, 1), (1, 87400, 0), (130, 43688, 1), (130, 43700, 0)])
+def test_joined_launch_holds_fewer_than_2_32_threads(n, hkv, joined):
+    """128 requests of one item per KV head in narrow work groups of 384 threads
+    and in full ones of 768: two launches where one would wrap its grid."""
+    R = 128
+    B = binding.make_branches(np.arange(R + 1), [0] * R, [0] * R, [n] * R)
+    got = _launches(_batch([60] * R, [n] * R, hq=hkv, hkv=hkv, D=64), B)
+    assert (got.joined_launches, got.launches, got.narrow) == (joined, 2 - joined, n == 1)
+
+
+@pytest.mark.parametrize("n,hkv,status", [(1, 87376, 0), (1, 87400, 3), (130, 43688, 0), (130, 43700, 3)])
+def test_launches_of_2_32_threads_are_refused(n, hkv, status):
+    l = _batch([60] * 128, [n] * 128, hq=hkv, hkv=hkv, D=64)
+    size = ctypes.c_size_t()
+    assert binding.library().rg_draft_verify_attention_workspace(ctypes.byref(l.c), ctypes.byref(size)) == status
