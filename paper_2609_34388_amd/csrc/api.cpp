@@ -338,29 +338,47 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
   // the long items start early and the short ones fill in at the end.  An
   // item's time is estimated in units of one 128-key buffer at the copy rate:
   // about two units of start-up plus its buffers, each costing tile_weight
-  // units.  A request's items all
-  // get the estimate of its widest column group's full-chunk item.  The
-  // divisor was picked by measurement: against ordering by keys alone, over 4
+  // units.  A request's items all get the estimate of its widest column
+  // group's longest item.  The divisor was picked by measurement: against ordering by keys alone, over 4
   // `long` and 10 `mid` draws, the divisors 4 and 5.6 and a linear
   // 1 + tiles / 8 gave `long` -3.1, -0.8 and -3.5 %, `mid` -1.6, -1.8 and
   // -1.2 %, and `high` (narrow items) +0.2, +0.2 and +0.7 %.
   std::vector<double> cost(R);
-  for (int r = 0; r < R; ++r) {
-    const int64_t n = L->q_indptr[r + 1] - L->q_indptr[r];
-    const int64_t T = (int64_t)L->ctx_len[r] + n;
-    const int64_t all_tiles = (n * g + 31) / 32;
-    const int64_t groups = std::max<int64_t>(1, (all_tiles + 7) / 8);
-    const int64_t tiles = (all_tiles + groups - 1) / groups;  // the widest column group's (tiles dealt evenly)
-    const int64_t bufs = (std::min<int64_t>(T, fp.run) + kKeyTile - 1) / kKeyTile;
-    cost[r] = n == 0 ? 0.0 : 2.0 + (double)bufs * tile_weight(tiles);
-  }
-  std::vector<int> order(R);
-  for (int r = 0; r < R; ++r) order[r] = r;
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+  auto cost_of_items = [&](int keys) {  // of at most this many keys
+    for (int r = 0; r < R; ++r) {
+      const int64_t n = L->q_indptr[r + 1] - L->q_indptr[r];
+      const int64_t T = (int64_t)L->ctx_len[r] + n;
+      const int64_t all_tiles = (n * g + 31) / 32;
+      const int64_t groups = std::max<int64_t>(1, (all_tiles + 7) / 8);
+      const int64_t tiles = (all_tiles + groups - 1) / groups;  // the widest column group's (tiles dealt evenly)
+      const int64_t bufs = (std::min<int64_t>(T, keys) + kKeyTile - 1) / kKeyTile;
+      cost[r] = n == 0 ? 0.0 : 2.0 + (double)bufs * tile_weight(tiles);
+    }
+  };
+  auto costlier = [&](int x, int y) {
     if (cost[x] != cost[y]) return cost[x] > cost[y];
     return (int64_t)L->ctx_len[x] + (L->q_indptr[x + 1] - L->q_indptr[x]) >
            (int64_t)L->ctx_len[y] + (L->q_indptr[y + 1] - L->q_indptr[y]);
-  });
+  };
+  std::vector<int> order(R);
+  for (int r = 0; r < R; ++r) order[r] = r;
+  // Several launches share the workspace, whose size is that of the launches
+  // at its own split, alike in both launch modes: `split` is their order.  A
+  // longer run's launches take the requests in that run's order, all of them
+  // where no request is split (no partials), else each launch its own, whose
+  // partials are then no more than the split's.
+  std::vector<int> split;
+  int64_t per = R;
+  if (R > MaxReq && fp.run != fp.chunk) {
+    cost_of_items(fp.chunk);
+    std::stable_sort(order.begin(), order.end(), costlier);
+    split = order;
+    for (const PairLoad& p : pairs)
+      if (p.keys > fp.run) per = MaxReq;
+  }
+  cost_of_items(fp.run);
+  for (int64_t r0 = 0; r0 < R; r0 += per)
+    std::stable_sort(order.begin() + r0, order.begin() + std::min<int64_t>(R, r0 + per), costlier);
   for (int r0 = 0; r0 < R; r0 += MaxReq) {
     const int cnt = std::min(MaxReq, R - r0);
     Plan p;
@@ -369,8 +387,8 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
     p.chunk = fp.run;
     p.cols_per_group = fp.cols_per_group;
     p.narrow = fp.narrow ? 1 : 0;
-    int64_t items = 0, part = 0, comb = 0;    // of the launch
-    int64_t plan_items = 0, plan_part = 0;    // at the workspace's split
+    int64_t items = 0, part = 0, comb = 0, run_split_requests = 0;  // of the launch
+    int64_t plan_items = 0, plan_part = 0, split_requests = 0;      // at the workspace's split
     for (int k = 0; k < cnt; ++k) {
       const int r = order[r0 + k];
       const int64_t n = L->q_indptr[r + 1] - L->q_indptr[r];
@@ -389,22 +407,34 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
       const int64_t nch = (T + fp.run - 1) / fp.run;
       const int64_t ncg = (M + fp.cols_per_group - 1) / fp.cols_per_group;
       items += hkv * ncg * nch;
-      const int64_t plan_nch = (T + fp.chunk - 1) / fp.chunk;
-      plan_items += hkv * ncg * plan_nch;
-      if (plan_nch > 1) {
-        plan_part += hkv * plan_nch * round_up(M, 32);
-        fp.split_requests += 1;
-      }
       if (nch > 1) {
-        fp.run_split_requests += 1;
+        run_split_requests += 1;
         p.max_chunks = std::max<int32_t>(p.max_chunks, (int32_t)nch);
         // partials are stored per 32-column tile, so columns round up to 32
         part += hkv * nch * round_up(M, 32);
         comb += hkv * ((M + 31) / 32) * (L->head_dim * 4 / comb_rows);  // slices of a tile's 4 D rows
       }
-      if (plan_items > INT32_MAX / 2 || plan_part > INT32_MAX / 2) return RG_ERR_UNSUPPORTED;
-      if (part > plan_part) return RG_ERR_WORKSPACE;  // run >= chunk: the partials fit the workspace
+      if (items > INT32_MAX / 2 || part > INT32_MAX / 2) return RG_ERR_UNSUPPORTED;
     }
+    for (int k = 0; k < cnt && fp.run != fp.chunk; ++k) {
+      const int r = split.empty() ? order[r0 + k] : split[r0 + k];
+      const int64_t n = L->q_indptr[r + 1] - L->q_indptr[r];
+      if (n == 0) continue;
+      const int64_t M = n * g;
+      const int64_t nch = ((int64_t)L->ctx_len[r] + n + fp.chunk - 1) / fp.chunk;
+      plan_items += hkv * ((M + fp.cols_per_group - 1) / fp.cols_per_group) * nch;
+      if (nch > 1) {
+        plan_part += hkv * nch * round_up(M, 32);
+        split_requests += 1;
+      }
+      if (plan_items > INT32_MAX / 2 || plan_part > INT32_MAX / 2) return RG_ERR_UNSUPPORTED;
+    }
+    if (fp.run == fp.chunk) {
+      plan_items = items;
+      plan_part = part;
+      split_requests = run_split_requests;
+    }
+    if (part > plan_part) return RG_ERR_WORKSPACE;  // run >= chunk: the partials fit the workspace
     p.req[cnt].item_start = (int32_t)items;
     p.req[cnt].part_start = (int32_t)part;
     p.req[cnt].comb_start = (int32_t)comb;
@@ -419,6 +449,8 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
       fp.persistent_launches += 1;
     }
     fp.items += plan_items;
+    fp.split_requests += split_requests;
+    fp.run_split_requests += run_split_requests;
     fp.max_partial_cols = std::max(fp.max_partial_cols, plan_part);
     fp.total_partial_cols += plan_part;
     fp.run_max_partial_cols = std::max(fp.run_max_partial_cols, part);

@@ -259,3 +259,27 @@ def test_launches_of_2_32_threads_are_refused(n, hkv, status):
     l = _batch([60] * 128, [n] * 128, hq=hkv, hkv=hkv, D=64)
     size = ctypes.c_size_t()
     assert binding.library().rg_draft_verify_attention_workspace(ctypes.byref(l.c), ctypes.byref(size)) == status
+
+
+def test_workspace_size_does_not_depend_on_the_launch_mode(monkeypatch):
+    """More than 128 requests fill several launches that share the workspace;
+    one sized in either mode serves the other."""
+    longer = 0
+    for seed in [53, 126, 132, 150, *range(200, 300)]:
+        rng = np.random.default_rng(seed)
+        R = int(rng.integers(129, 257))
+        base = int(rng.integers(300, 3000))
+        ctx = rng.integers(base, base + int(2 ** rng.uniform(5, 10)), R)
+        n = rng.choice([1, 16, 22], R, p=[0.4, 0.3, 0.3])  # one, four and six tiles of columns
+        l = _batch(ctx, n, hq=8, hkv=1)
+        B = binding.make_branches(np.arange(R + 1), [0] * R, [0] * R, n)
+        size = {}
+        for mode in ("1", "0"):
+            monkeypatch.setenv("RG_ATTN_PERSIST", mode)
+            branched = ctypes.c_size_t()
+            assert binding.library().rg_multibranch_attention_workspace(ctypes.byref(l.c), ctypes.byref(B.c),
+                                                                        ctypes.byref(branched)) == 0
+            size[mode] = (_plan(l).workspace_bytes, branched.value)
+        longer += _launches(l).run_keys > _plan(l).chunk_keys
+        assert size["0"] == size["1"], seed
+    assert longer > 20
