@@ -269,17 +269,19 @@ int choose_run(const std::vector<PairLoad>& pairs, int hkv, int num_cus, int chu
 // take short items; at head size 64, where a buffer is half the bytes and the
 // softmax is the longer part, also every call of more than one round; and at
 // 128, where items have one or two tiles and the copies are the longer part,
-// also medium ones.  Measured on 160 drawn batches with both kinds (GPU time
-// of the call, full over narrow):
-//   items of at most 512 keys, more than one round: 1.13 to 1.37 (70 requests
+// also medium ones.  Measured with both kinds (GPU time of the call, full over
+// narrow).  160 drawn batches at D = 64 and 128:
+//   items of at most 512 keys, more than one round: 1.10 to 1.40 (70 requests
 //     of 140 to 500 keys, 42.6 and 31.2 us);
-//   at most one round: to 512 keys at D = 64 1.02 to 1.14, to 256 at D = 128
-//     1.02 to 1.15, where 384 keys of 3 or 4 tiles give 0.97 to 1.02;
-//   D = 64, more than one round: 1.015 to 1.27; at most one round of longer
-//     items: 0.89 to 0.98;
-//   D = 128, one or two tiles, up to 2432 keys: 1.02 to 1.34; longer: 0.96 to
-//     1.02;
-//   D = 128, three or four tiles, longer items: 0.79 to 1.02.
+//   D = 64, at most one round: to 512 keys 1.02 to 1.14, longer 0.89 to 0.98;
+//     more than one round: 1.015 to 1.27.
+// 130 batches at D = 128:
+//   at most one round of three or four tiles: 256 keys 1.00 to 1.09 (mean
+//     1.05), 384 keys 0.96 to 1.08 (1.02), 512 keys 0.94 to 1.03 (0.99),
+//     longer 0.91 to 1.00;
+//   more than one round of three or four tiles: 640 keys 1.06 to 1.10, 768 to
+//     1280 keys 0.97 to 1.06, longer 0.89 to 0.93;
+//   one or two tiles: to 2432 keys 1.00 to 1.40; longer 0.96 to 1.10.
 bool narrow_items(const std::vector<PairLoad>& pairs, int hkv, int num_cus, int head_dim, int run) {
   int64_t items = 0, tiles = 0;
   for (const PairLoad& p : pairs) {

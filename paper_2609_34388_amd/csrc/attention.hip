@@ -543,6 +543,10 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
     }
     __builtin_amdgcn_sched_barrier(0);  // keep the next sub-tile's loads after this one's PV
   };
+  // Rolled, but for the narrow group at D = 64: unrolled, its two sub-tiles at
+  // D = 128 need more than the 168 registers of three waves per SIMD (20 bytes
+  // of scratch per lane, 544 KiB written in a call of 136 items).
+  constexpr int kSubTileUnroll = D == 64 && NW == kNarrowWaves ? 2 : 1;
   for (int s = 0; s < nsup; ++s) {
     lds_barrier();
     const int k0 = kbeg + s * KEYS;
@@ -552,6 +556,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, cons
       const uint16_t* kt = kbuf(s);
       const uint16_t* vt = vbuf(s);
       // this wave's sub-tiles of the buffer: global sub-tile j = KEYS / 32 s + q with j % kg == kgi
+#pragma unroll kSubTileUnroll
       for (int q = 0; q < KEYS / 32; ++q)
         if (((KEYS / 32 * s + q) & (kg - 1)) == kgi && 32 * q < nvalid) softmax_pv(qk(kt, q), k0 + 32 * q, vt, q);
     }
