@@ -243,6 +243,7 @@ def overlap_leg(lay, dev, steps, warmup, capture, timed, step_outputs, quadratic
     result = {
         "branches": len(flat), "requests": lay.num_requests, "rows": ov.total_q,
         "kv_tokens": int(ov.kv_len.sum()), "input_copies_rotated": copies,
+        "launches": binding.attention_launches(lays_ov[0], B),
         "multibranch": {"us": round(mb_ms * 1e3, 3), "bytes": ov_bytes, "flops": ov_flops,
                         "gbps": round(ov_bytes / (mb_ms * 1e-3) / 1e9, 1),
                         "frac_hbm": round(ov_bytes / (mb_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),

@@ -182,7 +182,11 @@ def overlap_md(out: str, wl: str) -> str:
     ff, wf = cal["FETCH_SIZE"][2], cal["WRITE_SIZE"][2]
     fetch = per_kernel(counter_rows(one(f"{out}/pmc_FETCH_SIZE_{tag}/*counter_collection.csv")), "FETCH_SIZE")
     write = per_kernel(counter_rows(one(f"{out}/pmc_WRITE_SIZE_{tag}/*counter_collection.csv")), "WRITE_SIZE")
-    launches = (ov["requests"] + 63) // 64  # the branched plan holds 64 requests per launch
+    # Dispatches per call by kind of kernel, as the library says it launches them.
+    run = ov["launches"]
+    per_call = {"joined": run["joined_launches"], "main": run["launches"] - run["joined_launches"],
+                "merge": run["merge_launches"]}
+    kind = lambda k: "merge" if "combine" in k else "joined" if "AttnReqBrPacked" in k else "main"
     lines = [f"# Multi-branch attention of the overlap round, workload `{wl}`: kernel trace and HBM traffic", "",
              f"The overlap round of the benchmark on `{wl}` ({ov['requests']} requests, {ov['branches']} branches, "
              f"{ov['rows']} query rows, {ov['kv_tokens']} keys): every request keeps its verify rows and gets two "
@@ -201,19 +205,21 @@ def overlap_md(out: str, wl: str) -> str:
         n = short(r["Name"])
         if "AttnReqBr" in n or "branches_kernel" in n:
             lines.append(f"| {n} | {r['Calls']} | {float(r['AverageNs']) / 1e3:.2f} |")
-    by = 0.0
     fk = wk = 0.0
-    for k in fetch:
-        if "AttnReqBr" in k:
-            f_, w_ = statistics.mean(fetch[k]), statistics.mean(write.get(k, [0.0]))
-            fk += f_
-            wk += w_
-            by += (f_ * ff + w_ * wf) * 1024
-    by *= launches  # every branched kernel runs once per launch
-    fk *= launches
-    wk *= launches
+    for k, n in per_call.items():
+        for c, got in (("FETCH_SIZE", fetch), ("WRITE_SIZE", write)):
+            vals = [v for name in got if "AttnReqBr" in name and kind(name) == k for v in got[name]]
+            if n and not vals:
+                raise ValueError(f"no {k} dispatch of a branched attention kernel in the {c} pass")
+            kib = n * statistics.mean(vals) if n else 0.0
+            if c == "FETCH_SIZE":
+                fk += kib
+            else:
+                wk += kib
+    by = (fk * ff + wk * wf) * 1024
     alg = ov["multibranch"]["bytes"]
-    lines += ["", f"rg_multibranch_attention = {launches} launch(es) per call (at most 64 requests per launch).", "",
+    lines += ["", f"rg_multibranch_attention = {run['launches']} main launch(es) per call ({run['joined_launches']} of two "
+              f"plans of up to 64 requests), {run['merge_launches']} merge launch(es).", "",
               "| per call | FETCH_SIZE KiB | WRITE_SIZE KiB | HBM MB (scaled) | algorithmic MB | ratio |",
               "|---|---|---|---|---|---|",
               f"| rg_multibranch_attention | {fk:.0f} | {wk:.0f} | {by / 1e6:.1f} | {alg / 1e6:.1f} | {by / alg:.3f} |",
