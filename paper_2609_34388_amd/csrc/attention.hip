@@ -146,6 +146,11 @@ constexpr int kKBufs = 2;    // K buffers: one computed, one being filled
 constexpr int kVBufs = 2;    // V buffers: one computed, one being filled
 static_assert(kKBufs == 2 && kVBufs == 2, "two copy-wave pairs, one per buffer parity and LDS slot");
 
+// Request r of a plan.
+__device__ __forceinline__ AttnReq request_of(const AttnPlan& p, int r) { return p.req[r]; }
+__device__ __forceinline__ AttnReqBr request_of(const AttnPlanBr& p, int r) { return p.req[r]; }
+__device__ __forceinline__ AttnReqBr request_of(const AttnPlanBrPacked& p, int r) { return p.req[r].unpack(); }
+
 // A full work group (NW = 8) takes up to 256 columns and has a CU to itself.
 // A narrow one (NW = 4, launches without a request of more than 128 columns)
 // halves everything per group: waves, columns, keys per buffer and LDS, so
@@ -175,10 +180,6 @@ static_assert(kKBufs == 2 && kVBufs == 2, "two copy-wave pairs, one per buffer p
 // then passes the same barriers (the copy waves join the key-group merge),
 // and a split item's partials are stored device-coherently and counted so
 // that the combine items of the same launch can merge them.
-__device__ __forceinline__ AttnReq request_of(const AttnPlan& p, int r) { return p.req[r]; }
-__device__ __forceinline__ AttnReqBr request_of(const AttnPlanBr& p, int r) { return p.req[r]; }
-__device__ __forceinline__ AttnReqBr request_of(const AttnPlanBrPacked& p, int r) { return p.req[r].unpack(); }
-
 template <int D, typename Plan, bool PERSIST, int NW>
 __device__ __forceinline__ void attn_item(const AttnArgs& a, const Plan& p, const int item, uint16_t* lds) {
   constexpr bool BR = !__is_same(Plan, AttnPlan);  // rows after the verify rows form branches
