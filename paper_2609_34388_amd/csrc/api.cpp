@@ -310,8 +310,8 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
                          int num_cus) {
   const int R = L->num_requests;
   const bool persist = env_int("RG_ATTN_PERSIST", 0) != 0;
-  // 16-byte rows per combine item: 128 (combine kernel), 256 (one-launch kernel)
-  const int comb_rows = persist ? 256 : 128;
+  // 16-byte rows per combine item: 128 (combine kernel, a thread each), 256 (one-launch kernel)
+  const int comb_rows = persist ? 256 : kCombThreads;
   const int g = L->num_q_heads / L->num_kv_heads;
   const int hkv = L->num_kv_heads;
   fp.cols_per_group = 256;  // 8 waves x 32 columns per work group
@@ -441,6 +441,11 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
       split_requests = run_split_requests;
     }
     if (part > plan_part) return RG_ERR_WORKSPACE;  // run >= chunk: the partials fit the workspace
+    const bool one_launch = persist && comb > 0 && comb <= kMaxSyncComb;
+    if (persist && !one_launch) {  // the merge kernel's items are half as long
+      for (int k = 0; k < cnt; ++k) p.req[k].comb_start *= 256 / kCombThreads;
+      comb *= 256 / kCombThreads;
+    }
     p.req[cnt].item_start = (int32_t)items;
     p.req[cnt].part_start = (int32_t)part;
     p.req[cnt].comb_start = (int32_t)comb;
@@ -448,7 +453,7 @@ rg_status plan_attention(const rg_attn_layout* L, const rg_branch_layout* B, Ful
     p.total_comb = (int32_t)comb;
     p.grid_items = (int32_t)round_up(items, 8);
     p.grid_comb = (int32_t)round_up(comb, 8);
-    if (!(persist && comb > 0 && comb <= kMaxSyncComb)) {
+    if (!one_launch) {
       if (!fits_launch(items, item_threads(fp.narrow)) || !fits_launch(comb, kCombThreads)) return RG_ERR_UNSUPPORTED;
     } else {
       p.persist_grid = (int32_t)round_up(std::min<int64_t>(items + comb, std::max(8, num_cus)), 8);

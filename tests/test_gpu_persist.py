@@ -190,3 +190,30 @@ def test_many_requests_several_persistent_launches(monkeypatch):
     torch.cuda.synchronize()
     check(out, lse, reference(lay, inp))
     assert int(_sync_words(ws, info).abs().sum()) == 0
+
+
+@pytest.mark.parametrize("D,rows,one_launch", [(128, 64, 1), (128, 68, 0), (64, 128, 1), (64, 136, 0)])
+def test_merge_items_past_the_counters(monkeypatch, D, rows, one_launch):
+    """128 requests with 16384 merge items (the most that one launch counts)
+    and with more, which take the two kernels also in one-launch mode: every
+    output is written."""
+    monkeypatch.setenv("RG_ATTN_PERSIST", "1")
+    monkeypatch.setenv("RG_ATTN_CHUNK", "128")
+    R = 128
+    lay = _custom(R, [100] * R, [rows // 4] * R, [rows - rows // 4] * R, hq=32, hkv=8, D=D, seed=61)
+    inp = W.make_attention_inputs(lay, DEV, poison=float("nan"))
+    handle = _layout_handle(lay, inp)
+    info = binding.attention_plan(handle)
+    launches = binding.attention_launches(handle)
+    assert info["persistent_launches"] == one_launch and launches["merge_launches"] == 1 - one_launch
+    ws = binding.new_workspace(info["workspace_bytes"], DEV)
+    out = torch.full_like(inp["q"], float("nan"))
+    lse = torch.full(out.shape[:2], float("nan"), dtype=torch.float32, device=DEV)
+    binding.draft_verify_attention(inp["q"], inp["k_cache"], inp["v_cache"], None, None, None, None, None, out=out,
+                                   lse=lse, workspace=ws, layout=handle)
+    torch.cuda.synchronize()
+    assert torch.isfinite(out.float()).all() and torch.isfinite(lse).all()
+    sample = [0, 64, 127]
+    picked = np.concatenate([np.arange(lay.q_indptr[r], lay.q_indptr[r + 1]) for r in sample])
+    check(out, lse, reference(lay, inp, requests=sample), rows=picked)
+    assert int(_sync_words(ws, info).abs().sum()) == 0
