@@ -21,8 +21,8 @@ namespace {
 constexpr int kPlanWaves = 4;
 
 __global__ __launch_bounds__(64 * kPlanWaves) void plan_branches_kernel(PlanBranchArgs a) {
-  const int r = (int)blockIdx.x * kPlanWaves + (int)(threadIdx.x >> 6);  // wave-uniform
-  if (r >= a.num_req) return;
+  const uint32_t r = ((uint32_t)a.first + blockIdx.x) * kPlanWaves + (threadIdx.x >> 6);  // wave-uniform
+  if (r >= (uint32_t)a.num_req) return;
   const int lane = threadIdx.x & 63;
   const int k0 = a.row_indptr[r], n = a.row_indptr[r + 1] - k0;
   int count = 0, p0 = -1, p1 = -1;
@@ -40,10 +40,10 @@ __global__ __launch_bounds__(64 * kPlanWaves) void plan_branches_kernel(PlanBran
   if (lane == 0) {
     a.n_risky[r] = count;
     a.n_corr[r] = min(count, 2);
-    a.corr_pos[2 * r] = p0;
-    a.corr_pos[2 * r + 1] = p1;
-    a.corr_tok[2 * r] = p0 >= 0 ? a.top2[k0 + p0] : -1;
-    a.corr_tok[2 * r + 1] = p1 >= 0 ? a.top2[k0 + p1] : -1;
+    a.corr_pos[2 * (size_t)r] = p0;
+    a.corr_pos[2 * (size_t)r + 1] = p1;
+    a.corr_tok[2 * (size_t)r] = p0 >= 0 ? a.top2[k0 + p0] : -1;
+    a.corr_tok[2 * (size_t)r + 1] = p1 >= 0 ? a.top2[k0 + p1] : -1;
     a.continuation[r] = count <= 2 ? 1 : 0;
   }
 }
@@ -62,9 +62,10 @@ __global__ __launch_bounds__(256) void match_branches_kernel(MatchBranchArgs a) 
 }  // namespace
 
 hipError_t launch_plan_branches(const PlanBranchArgs& a, hipStream_t stream) {
-  const int blocks = (a.num_req + kPlanWaves - 1) / kPlanWaves;
-  hipLaunchKernelGGL(plan_branches_kernel, dim3(blocks), dim3(64 * kPlanWaves), 0, stream, a);
-  return hipGetLastError();
+  const int64_t groups = ((int64_t)a.num_req + kPlanWaves - 1) / kPlanWaves;
+  return sliced(a, groups, 64 * kPlanWaves, [&](const PlanBranchArgs& s) {
+    hipLaunchKernelGGL(plan_branches_kernel, dim3(s.grid), dim3(64 * kPlanWaves), 0, stream, s);
+  });
 }
 
 hipError_t launch_match_branches(const MatchBranchArgs& a, hipStream_t stream) {

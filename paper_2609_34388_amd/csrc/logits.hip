@@ -25,7 +25,6 @@
 // mismatch.  The kernel boundary is the
 // only cross-work-group synchronisation: no atomics, no device-scope fences,
 // and the workspace needs no initialisation.
-#include <algorithm>
 #include <mutex>
 
 #include "rg_internal.h"
@@ -620,24 +619,6 @@ __global__ __launch_bounds__(kFinalizeThreads) void round_finalize_kernel(Verify
   const uint32_t b = (uint32_t)v.first + blockIdx.x;
   if (b < (uint32_t)v.num_req) verify_finalize(v, (int)b, lds);
   else draft_finalize(d, (int)(b - (uint32_t)v.num_req));
-}
-
-// Calls launch(args) for consecutive slices of `groups` work groups of
-// `threads` threads, args.first and args.grid telling the slice: one up to
-// 2^23 - 8 requests or 2^24 - 8 row chunks.  Slices are whole multiples of 8
-// groups (xcd_item).  The slice travels in the argument structs' padding: as two
-// more kernel arguments it cost 1 % of a pass over 2000 rows of 128256.
-template <typename Args, typename Launch>
-hipError_t sliced(Args args, int64_t groups, int threads, Launch launch) {
-  const int64_t most = kMaxLaunchThreads / threads / 8 * 8;
-  for (int64_t first = 0; first < groups; first += most) {
-    args.first = (int32_t)(uint32_t)first;
-    args.grid = (int32_t)std::min(most, groups - first);
-    launch(args);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
 }
 
 int draft_finalize_groups(const DraftArgs& a) {

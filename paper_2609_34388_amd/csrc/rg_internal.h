@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 
@@ -145,6 +146,25 @@ hipError_t launch_attention(const AttnArgs& args, const AttnPlanBr& plan, int he
 hipError_t launch_attention(const AttnArgs& args, const AttnPlanBrPacked& plan, int head_dim,
                             hipStream_t stream);
 
+// Calls launch(args) for consecutive slices of `groups` work groups of
+// `threads` threads, args.first and args.grid telling the slice: one up to
+// 2^23 - 8 requests or 2^24 - 8 row chunks of the logit passes and 2^26 - 32
+// requests of the branch plan.  Slices are whole multiples of 8 groups
+// (xcd_item).  The slice travels in the argument structs' padding: as two
+// more kernel arguments it cost 1 % of a logit pass over 2000 rows of 128256.
+template <typename Args, typename Launch>
+hipError_t sliced(Args args, int64_t groups, int threads, Launch launch) {
+  const int64_t most = kMaxLaunchThreads / threads / 8 * 8;
+  for (int64_t first = 0; first < groups; first += most) {
+    args.first = (int32_t)(uint32_t)first;
+    args.grid = (int32_t)std::min(most, groups - first);
+    launch(args);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Logit-row reductions (logits.hip).
 constexpr int kLogitThreads = 256;
 constexpr int kLogitChunk = 8192;  // vocab entries per work group
@@ -226,6 +246,7 @@ struct PlanBranchArgs {
   int32_t* corr_pos;
   int32_t* corr_tok;
   int32_t* continuation;
+  int32_t grid, first;  // as in VerifyArgs
 };
 struct MatchBranchArgs {
   const int32_t* accept_len;

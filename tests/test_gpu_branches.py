@@ -354,3 +354,26 @@ def test_quadratic_layout_full_size_low_shape():
                                          ov.page_indptr, ov.page_indices, branches, heads=heads)
     for h in heads:
         _check(out[:, h:h + 1], lse[:, h:h + 1], dict(out=ref["out"][:, h:h + 1], lse=ref["lse"][:, h:h + 1]))
+
+
+def test_plan_branches_past_the_threads_of_a_grid():
+    """2^26 + 9 requests, a wavefront each: more than the 2^32 threads of one
+    launch.  All but a few requests are empty; every output is written."""
+    R, rows = (1 << 26) + 9, 24
+    owners = [0, (1 << 26) - 40, (1 << 26) - 1, 1 << 26, R - 1]
+    counts = [8, 4, 3, 1, 8]
+    rp = torch.zeros(R + 1, dtype=torch.int32, device=DEV)
+    at = 0
+    for r, n in zip(owners, counts):
+        at += n
+        rp[r + 1:] = at
+    rng = np.random.default_rng(3)
+    margin, top2 = rng.random(rows).astype(np.float32), rng.integers(0, 1000, rows).astype(np.int32)
+    e = lambda *s: torch.full(s, -7, dtype=torch.int32, device=DEV)
+    out = dict(n_risky=e(R), n_corr=e(R), corr_pos=e(R, 2), corr_tok=e(R, 2), continuation=e(R))
+    got = binding.plan_branches(torch.as_tensor(margin, device=DEV), torch.as_tensor(top2, device=DEV), rp, 0.3, out=out)
+    want = oracle.oracle_plan_branches(margin, top2, np.concatenate([[0], np.cumsum(counts)]), 0.3)
+    for k in got:
+        np.testing.assert_array_equal(got[k][owners].cpu().numpy(), np.asarray(want[k]).reshape(got[k][owners].shape), k)
+        empty = {"n_risky": 0, "n_corr": 0, "corr_pos": -1, "corr_tok": -1, "continuation": 1}[k]
+        assert int((got[k] != empty).sum()) == int((got[k][owners] != empty).sum()), k
